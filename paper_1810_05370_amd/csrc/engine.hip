@@ -739,7 +739,7 @@ int pcg_iterate(Ctx& c, tumor::KrylovArgs a, Apply apply, double thr2, int limit
   a.limit = limit;
   a.fixed = fixed ? 1 : 0;
   a.dpart = c.dpart;
-  a.dnb = tumor::col_pass_blocks<R>(c.n, 2);
+  a.dnb = tumor::col_pass_blocks<R>(c.n, 2, a.ncomp);
   a.dstride = 1;
   const int kc = kcls<R>(TUMOR_K_KRYLOV64, TUMOR_K_KRYLOV32);
   const double vb = double(a.ncomp) * double(c.V) * sizeof(R);  // one Krylov vector
@@ -1053,7 +1053,7 @@ void pcg_iterate_b(Ctx& c, tumor::BatchArgs a, const double* thr2, const int* li
   }
   if (any_fixed) chunk = std::min(lim_max, 64);
   a.dpart = c.dpart;
-  a.dnb = tumor::col_pass_blocks<R>(c.n, 2);
+  a.dnb = tumor::col_pass_blocks<R>(c.n, 2, 1);
   const int kc = kcls<R>(TUMOR_K_KRYLOV64, TUMOR_K_KRYLOV32);
   const double vb = double(c.V) * sizeof(R);  // one system's Krylov vector
   const int nact = __builtin_popcount((unsigned)a.active);

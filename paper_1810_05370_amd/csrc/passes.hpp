@@ -27,6 +27,10 @@ namespace tumor {
 
 constexpr int kMaxCol = 9;
 constexpr int kMaxTerms = 3;
+// Grids up to this size share the outputs of a pass out over grid layers.  A
+// pass at 64^3 or below has at most 64 column tiles or 256 row waves, far too
+// few to fill 256 CUs, and lasts as long as one block's chain of transforms.
+constexpr int kSplitMaxN = 64;
 
 enum ColSym : int { SYM_ONE = 0, SYM_IW = 1, SYM_RAW = 2 };
 
@@ -175,8 +179,9 @@ template <typename R>
 void launch_xforce(int n, const XForceArgs& a, const void* tw, hipStream_t st);
 template <typename R>
 void launch_xdot(int n, const XDotArgs& a, const void* tw, hipStream_t st);
-// blocks of a column pass along `axis` (the count of its inner-product partials)
+// inner-product partials of a column pass along `axis` with nout outputs that
+// share one product
 template <typename R>
-int col_pass_blocks(int n, int axis);
+int col_pass_blocks(int n, int axis, int nout);
 
 }  // namespace tumor

@@ -119,11 +119,18 @@ __global__ void __launch_bounds__((ColCfg<N, R, SEG>::THREADS), ((DOT && sizeof(
 #pragma unroll
     for (int j = 0; j < 8; ++j) dst[j] = sp[base + (long long)(t + TP * j) * astride];
   };
-  // outputs to compute (block-uniform): all but those of converged systems
+  // outputs to compute (block-uniform): this grid layer's share (see
+  // col_split), without those of converged systems
   unsigned am = 0;
-  for (int o = 0; o < prog.nout; ++o)
+  for (int o = blockIdx.z; o < prog.nout; o += gridDim.z)
     if (!(prog.oskip[o] && *prog.oskip[o])) am |= 1u << o;
-  if (am == 0) return;
+  if (am == 0) {
+    if constexpr (DOT) {
+      // a layer without outputs still owns a partial
+      if (!prog.dot_nsys && tid == 0) prog.dpart[(long long)blockIdx.z * gridDim.x * gridDim.y + blk] = 0.0;
+    }
+    return;
+  }
   // the active output after o, or -1
   auto next_out = [&](int o) -> int {
     const unsigned rest = am & ~((2u << o) - 1u);
@@ -228,13 +235,14 @@ __global__ void __launch_bounds__((ColCfg<N, R, SEG>::THREADS), ((DOT && sizeof(
     }
   }
   if constexpr (DOT) {
-    static_assert((N / 2 / TC) * N * kDotStride <= kPartialsCount,
+    static_assert((N / 2 / TC) * N * kDotStride <= kPartialsCount &&
+                      (N / 2 / TC) * N * (N <= kSplitMaxN ? kMaxCol : 1) <= kPartialsCount,
                   "the inner-product partials of every block must fit the partials buffer");
     if (!prog.dot_nsys) {
       // Parseval weight: the packed kx = 0 column counts once, the others twice
       const int kxp = bx * TC + col;
       dotacc *= (kxp == 0) ? 1.0 : 2.0;
-      store_dot_partial(dotacc, prog.dpart, 1, 0, blk);
+      store_dot_partial(dotacc, prog.dpart, 1, 0, (long long)blockIdx.z * gridDim.x * gridDim.y + blk);
     }
   }
 }
@@ -264,6 +272,46 @@ __global__ void __launch_bounds__((ColCfg<N, R, 256>::THREADS))
   const cplx<R>* __restrict__ r = static_cast<const cplx<R>*>(a.r);
   cplx<R>* __restrict__ p = static_cast<cplx<R>*>(a.p);
   cplx<R>* __restrict__ x = static_cast<cplx<R>*>(a.x);
+  if constexpr (N <= kSplitMaxN && NC > 1) {
+    // a small grid's layers take one component each (see col_layers): M^-1 r
+    // needs every component of r, but p, x and the outputs only their own
+    const int c = blockIdx.z;
+    cplx<R> pc[8], rr[8][NC], xv[8];
+    // every load first: the stores below may alias them for all the compiler
+    // knows (FP64 at 32^3: 10.7 us with eight round trips to memory one after
+    // another, 8.2 us with one)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const long long idx = base + (long long)(t + TP * j) * astride;
+#pragma unroll
+      for (int b = 0; b < NC; ++b) rr[j][b] = r[b * S + idx];
+      pc[j] = p[c * S + idx];
+      xv[j] = x ? x[c * S + idx] : czero<R>();
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int n = t + TP * j;
+      const long long idx = base + (long long)n * astride;
+      cplx<R> zv[NC];
+      apply_prec<R, NC>(rr[j], zv, kx, ky, wavenum<N>(n), a.cs, a.pc);
+      const cplx<R> zc = c == 0 ? zv[0] : (c == 1 ? zv[1] : zv[2]);
+      const cplx<R> pv = pc[j];
+      if (x) x[c * S + idx] = {xv[j].x + alpha * pv.x, xv[j].y + alpha * pv.y};
+      pc[j] = {zc.x + beta * pv.x, zc.y + beta * pv.y};
+      p[c * S + idx] = pc[j];
+    }
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      cplx<R> acc[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[j] = d ? ciw(pc[j], R(wavenum<N>(t + TP * j))) : pc[j];
+      fft_block<R, N, true, 1>(acc, lds, t, tw);
+      cplx<R>* __restrict__ dst = static_cast<cplx<R>*>(a.out[2 * c + d]);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) dst[base + (long long)(t + TP * j) * astride] = acc[j];
+    }
+    return;
+  }
   cplx<R> pn[NC][8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
@@ -683,6 +731,89 @@ __global__ void __launch_bounds__(RowCfg<N>::THREADS, (sizeof(R) == 4 ? 3 : 2))
   }
 }
 
+// The same pass on small grids: the six outputs-and-their-inputs groups go to
+// grid layers (blockIdx.y), so a block's chain is at most 4 inverse and 2
+// forward row transforms instead of 9 and 9.  The diagonal stresses' layers
+// repeat the three diagonal strains, whose rows are in L2.  Each output's
+// arithmetic is that of k_xelast.  FP64 at 32^3: 17.8 -> 8.2 us per launch;
+// FP32 at 64^3: 20.2 -> 11.5 us.
+template <typename R, int N>
+__global__ void __launch_bounds__(RowCfg<N>::THREADS) k_xelast_layers(XElastArgs a, const cplx<R>* __restrict__ twg) {
+  if (a.skip && *a.skip) return;
+  TUMOR_ROW_SETUP(N)
+  const R invV = R(1.0) / (R(N) * R(N) * R(N));
+  const long long bs = row_tile() * RC::RW * L;
+  const int ro = rl * L;
+  auto in = [&](int f) { return static_cast<const cplx<R>*>(a.in[f]) + bs; };
+  auto out = [&](int f) { return static_cast<cplx<R>*>(a.out[f]) + bs; };
+  const cplx<R>* mu = static_cast<const cplx<R>*>(a.mu) + bs;
+  const cplx<R>* lam = static_cast<const cplx<R>*>(a.lam) + bs;
+  const cplx<R>* eta = static_cast<const cplx<R>*>(a.eta) + bs;
+  const int g = blockIdx.y;
+  if (g < 3) {
+    // s_xx with eta u_x (out 0), s_yy (out 4), s_zz (out 7)
+    cplx<R> ex[8], ey[8], ez[8];
+    row_c2r<R, N>(ex, in(0), true, nullptr, lds, t, tw, ro);
+    row_c2r<R, N>(ey, in(4), false, nullptr, lds, t, tw, ro);
+    row_c2r<R, N>(ez, in(7), false, nullptr, lds, t, tw, ro);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int p = t + TP * j;
+      const cplx<R> m = mu[ro + p], l = lam[ro + p];
+      const cplx<R> ax = {ex[j].x * invV, ex[j].y * invV}, by = {ey[j].x * invV, ey[j].y * invV},
+                    cz = {ez[j].x * invV, ez[j].y * invV};
+      const cplx<R> lt = {l.x * (ax.x + by.x + cz.x), l.y * (ax.y + by.y + cz.y)};
+      const cplx<R> d = g == 0 ? ax : (g == 1 ? by : cz);
+      ex[j] = {R(2) * m.x * d.x + lt.x, R(2) * m.y * d.y + lt.y};
+    }
+    row_r2c<R, N>(ex, lds, t, tw);
+    if (g > 0) {
+      store_row<R, N>(out(g == 1 ? 4 : 7), ex, t, ro);
+      return;
+    }
+    cplx<R> ux[8];
+    row_c2r<R, N>(ux, in(0), false, nullptr, lds, t, tw, ro);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const cplx<R> e = eta[ro + t + TP * j];
+      ux[j] = {e.x * ux[j].x * invV, e.y * ux[j].y * invV};
+    }
+    row_r2c<R, N>(ux, lds, t, tw);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) ux[j] = csub(ux[j], iwx<R, N>(ex[j], t + TP * j));
+    store_row<R, N>(out(0), ux, t, ro);
+    return;
+  }
+  if (g < 5) {
+    // s_xy with eta u_y (out 3, 1), s_xz with eta u_z (out 6, 2)
+    cplx<R> u[8], s[8];
+    row_c2r_two<R, N>(u, s, in(g == 3 ? 1 : 2), in(g == 3 ? 3 : 6), lds, t, tw, ro);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int p = t + TP * j;
+      const cplx<R> m = mu[ro + p], e = eta[ro + p];
+      s[j] = {m.x * s[j].x * invV, m.y * s[j].y * invV};
+      u[j] = {e.x * u[j].x * invV, e.y * u[j].y * invV};
+    }
+    row_r2c<R, N>(s, lds, t, tw);
+    store_row<R, N>(out(g == 3 ? 3 : 6), s, t, ro);
+    row_r2c<R, N>(u, lds, t, tw);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) u[j] = csub(u[j], iwx<R, N>(s[j], t + TP * j));
+    store_row<R, N>(out(g == 3 ? 1 : 2), u, t, ro);
+    return;
+  }
+  cplx<R> s[8];  // s_yz (out 5)
+  row_c2r<R, N>(s, in(5), false, nullptr, lds, t, tw, ro);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const cplx<R> m = mu[ro + t + TP * j];
+    s[j] = {m.x * s[j].x * invV, m.y * s[j].y * invV};
+  }
+  row_r2c<R, N>(s, lds, t, tw);
+  store_row<R, N>(out(5), s, t, ro);
+}
+
 template <typename R, int N>
 __global__ void __launch_bounds__(RowCfg<N>::THREADS) k_xdiff(XDiffArgs a, const cplx<R>* __restrict__ twg) {
   unsigned act = 0;  // fields to compute (block-uniform)
@@ -702,8 +833,9 @@ __global__ void __launch_bounds__(RowCfg<N>::THREADS) k_xdiff(XDiffArgs a, const
     const cplx<R> k = K[ro + t + TP * j];
     kr[j] = {k.x * invV, k.y * invV};
   }
+  // every row transform of the tile, or on small grids this layer's
 #pragma unroll 1
-  for (int e = 0; e < 3 * a.ns; ++e) {
+  for (int e = blockIdx.y; e < 3 * a.ns; e += gridDim.y) {
     const int f = e / 3, d = e - 3 * f;
     if (!(act & (1u << f))) continue;
     // each output row is written after its own input row has been read (the
@@ -804,13 +936,30 @@ __global__ void __launch_bounds__(RowCfg<N>::THREADS) k_xdot(XDotArgs a, const c
     default: throw std::runtime_error("unsupported grid size " + std::to_string(n)); \
   }
 
+// Grid layers of a column pass.  On small grids a pass lasts as long as one
+// block's chain of transforms, so each layer computes one output (FP64 at
+// 32^3: 9-10 -> 4.2-4.5 us per launch; FP32 at 64^3: 14-16 -> 7-8 us); an output
+// that overwrites an input would race with the other layers' reads, so such a
+// program keeps one layer.
+inline int col_layers(int n, const ColProg& prog) {
+  if (n > kSplitMaxN) return 1;
+  for (int o = 0; o < prog.nout; ++o)
+    for (int q = 0; q < prog.nout; ++q)
+      for (int k = 0; k < prog.nterm[q]; ++k)
+        if (prog.out[o] == prog.in[prog.term[q][k].src]) {
+          if (prog.dsv) throw std::logic_error("an inner-product pass must not overwrite its inputs");
+          return 1;
+        }
+  return prog.nout;
+}
+
 template <typename R, int NN, int SEG>
 void launch_col_pass_seg(int axis, bool inverse, const ColProg& prog, const cplx<R>* twp, hipStream_t st) {
   using Cfg = ColCfg<NN, R, SEG>;
   const long long C = NN / 2;
   const long long fstride = axis == 1 ? (long long)NN * C : C;
   const long long astride = axis == 1 ? C : (long long)NN * C;
-  dim3 grid(C / Cfg::TC, NN);
+  dim3 grid(C / Cfg::TC, NN, col_layers(NN, prog));
   if (inverse)
     hipLaunchKernelGGL((k_col_pass<R, NN, true, false, SEG>), grid, dim3(Cfg::THREADS), 0, st, prog, fstride,
                        astride, twp);
@@ -832,13 +981,13 @@ void launch_col_pass(int n, int axis, bool inverse, const ColProg& prog, const v
 }
 
 template <typename R>
-int col_pass_blocks(int n, int axis) {
+int col_pass_blocks(int n, int axis, int nout) {
   int nb = 0;
   TUMOR_DISPATCH_N(n, {
     if (col_seg<R>(axis) == 256) nb = (int)((NN / 2) / ColCfg<NN, R, 256>::TC) * NN;
     else nb = (int)((NN / 2) / ColCfg<NN, R, 128>::TC) * NN;
   });
-  return nb;
+  return n <= kSplitMaxN ? nb * nout : nb;
 }
 
 template <typename R>
@@ -852,7 +1001,8 @@ void launch_zinv_pupdate(int n, int ncomp, const ZPUpdateArgs& a, const void* tw
     else if (ncomp == 1)
       hipLaunchKernelGGL((k_zinv_pupdate<R, NN, 1>), grid, dim3(Cfg::THREADS), 0, st, a, twp);
     else
-      hipLaunchKernelGGL((k_zinv_pupdate<R, NN, 3>), grid, dim3(Cfg::THREADS), 0, st, a, twp);
+      hipLaunchKernelGGL((k_zinv_pupdate<R, NN, 3>), dim3(grid.x, grid.y, NN <= kSplitMaxN ? 3 : 1),
+                         dim3(Cfg::THREADS), 0, st, a, twp);
   });
 }
 
@@ -882,7 +1032,10 @@ void launch_xelast(int n, const XElastArgs& a, const void* tw, hipStream_t st) {
   const cplx<R>* twp = static_cast<const cplx<R>*>(tw);
   TUMOR_DISPATCH_N(n, {
     dim3 grid((NN * NN) / RowCfg<NN>::RW);
-    hipLaunchKernelGGL((k_xelast<R, NN>), grid, dim3(RowCfg<NN>::THREADS), 0, st, a, twp);
+    if constexpr (NN <= kSplitMaxN)
+      hipLaunchKernelGGL((k_xelast_layers<R, NN>), dim3(grid.x, 6), dim3(RowCfg<NN>::THREADS), 0, st, a, twp);
+    else
+      hipLaunchKernelGGL((k_xelast<R, NN>), grid, dim3(RowCfg<NN>::THREADS), 0, st, a, twp);
   });
 }
 
@@ -890,7 +1043,7 @@ template <typename R>
 void launch_xdiff(int n, const XDiffArgs& a, const void* tw, hipStream_t st) {
   const cplx<R>* twp = static_cast<const cplx<R>*>(tw);
   TUMOR_DISPATCH_N(n, {
-    dim3 grid((NN * NN) / RowCfg<NN>::RW);
+    dim3 grid((NN * NN) / RowCfg<NN>::RW, NN <= kSplitMaxN ? 3 * a.ns : 1);
     hipLaunchKernelGGL((k_xdiff<R, NN>), grid, dim3(RowCfg<NN>::THREADS), 0, st, a, twp);
   });
 }
