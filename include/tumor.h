@@ -357,6 +357,11 @@ enum {
   TUMOR_K_ZINVP64_1, TUMOR_K_ZINVP32_1,  /* fused first pass of a one-field CN solve      */
   TUMOR_K_ZINVPB64, TUMOR_K_ZINVPB32,    /* fused first pass of the batched CN solve of
                                             i, o and l                                 */
+  /* the elasticity iteration's two-kernel transforms (n = 256): spectral side
+     inverse (with the direction update), x side, spectral side forward (with the
+     residual update) */
+  TUMOR_K_TILEINV64, TUMOR_K_TILEINV32, TUMOR_K_TILEX64, TUMOR_K_TILEX32, TUMOR_K_TILEFWD64,
+  TUMOR_K_TILEFWD32,
   TUMOR_K_COUNT
 };
 int tumor_kernel_timer(tumor_ctx* ctx, int32_t kernel_class, int32_t enable);

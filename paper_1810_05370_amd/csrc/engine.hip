@@ -25,6 +25,7 @@
 #include "adjoint.hpp"
 #include "kernels.hpp"
 #include "passes.hpp"
+#include "tile.hpp"
 #include "tumor.h"
 
 namespace {
@@ -726,36 +727,21 @@ tumor::KrylovArgs kargs(Ctx& c, int ncomp, cplx<R>* x, tumor::SolveScalars* sv, 
   return a;
 }
 
-// Plain PCG iterations after the residual r and its norms are in place.
-// `apply(p, q, skip)` computes q = A p.  Iterations are queued in chunks
-// between scalar read-backs: first the predicted count + 1, then the count
-// that the residual reduction observed so far (from rr0, ||r||^2 at the
-// start) predicts, + 1.  Kernels of an iteration after convergence see the
-// device `done` flag and return at once, so the chunking changes only timing.
-template <typename R, typename Apply>
-int pcg_iterate(Ctx& c, tumor::KrylovArgs a, Apply apply, double thr2, int limit, bool fixed, int pred,
-                int zero_x, bool& conv, bool& bad, double rr0) {
-  a.thr2 = thr2;
-  a.limit = limit;
-  a.fixed = fixed ? 1 : 0;
-  a.dpart = c.dpart;
-  a.dnb = tumor::col_pass_blocks<R>(c.n, 2, a.ncomp);
-  a.dstride = 1;
-  const int kc = kcls<R>(TUMOR_K_KRYLOV64, TUMOR_K_KRYLOV32);
-  const double vb = double(a.ncomp) * double(c.V) * sizeof(R);  // one Krylov vector
-  timed(c, kc, (zero_x ? 3.0 : 2.0) * vb, [&] { tumor::launch_pcg_start<R>(a, zero_x, c.st); });
+// PCG iterations after the start (p, rho): `step(k)` queues iteration k.
+// Iterations are queued in chunks between scalar read-backs: first the
+// predicted count + 1, then the count that the residual reduction observed so
+// far (from rr0, ||r||^2 at the start) predicts, + 1.  Kernels of an iteration
+// after convergence see the device `done` flag and return at once, so the
+// chunking changes only timing.
+template <typename Step>
+int pcg_run(Ctx& c, tumor::SolveScalars* sv, Step step, double thr2, int limit, bool fixed, int pred, bool& conv,
+            bool& bad, double rr0) {
   int launched = 0;
   int chunk = fixed ? std::min(limit, 64) : std::max(1, std::min(limit, pred + 1));
-  tumor::SolveScalars* sv = a.sv;
-  const int* skip = &sv->done;
   for (;;) {
     for (int k = 0; k < chunk && launched < limit; ++k, ++launched) {
       c.cur_tag = launched;
-      // iteration k: (p = M^-1 r + beta p fused into the first pass for k > 0),
-      // q = A p with alpha = rho / <p, q> fused into the last pass, then x, r
-      Fuse fz{launched > 0, a.r, a.x, sv, a.pc};
-      apply(static_cast<const cplx<R>*>(a.p), static_cast<cplx<R>*>(a.q), skip, &fz);
-      timed(c, kc, 3.0 * vb, [&] { tumor::launch_pcg_update<R>(a, c.st); });
+      step(launched);
     }
     c.cur_tag = -1;
     HIPCHECK(hipGetLastError());
@@ -774,11 +760,122 @@ int pcg_iterate(Ctx& c, tumor::KrylovArgs a, Apply apply, double thr2, int limit
       if (std::isfinite(left)) chunk = std::max(1, std::min(32, (int)std::ceil(left) + 1));
     }
   }
-  timed(c, kc, 3.0 * vb, [&] { tumor::launch_pcg_xfinal<R>(a, c.st); });
   conv = c.hsv->conv != 0;
   bad = c.hsv->bad != 0;
   return c.hsv->it;
 }
+
+// Plain PCG after the residual r and its norms are in place.
+// `apply(p, q, skip)` computes q = A p.
+template <typename R, typename Apply>
+int pcg_iterate(Ctx& c, tumor::KrylovArgs a, Apply apply, double thr2, int limit, bool fixed, int pred,
+                int zero_x, bool& conv, bool& bad, double rr0) {
+  a.thr2 = thr2;
+  a.limit = limit;
+  a.fixed = fixed ? 1 : 0;
+  a.dpart = c.dpart;
+  a.dnb = tumor::col_pass_blocks<R>(c.n, 2, a.ncomp);
+  a.dstride = 1;
+  const int kc = kcls<R>(TUMOR_K_KRYLOV64, TUMOR_K_KRYLOV32);
+  const double vb = double(a.ncomp) * double(c.V) * sizeof(R);  // one Krylov vector
+  timed(c, kc, (zero_x ? 3.0 : 2.0) * vb, [&] { tumor::launch_pcg_start<R>(a, zero_x, c.st); });
+  // iteration k: (p = M^-1 r + beta p fused into the first pass for k > 0),
+  // q = A p with alpha = rho / <p, q> fused into the last pass, then x, r
+  const int it = pcg_run(
+      c, a.sv,
+      [&](int k) {
+        Fuse fz{k > 0, a.r, a.x, a.sv, a.pc};
+        apply(static_cast<const cplx<R>*>(a.p), static_cast<cplx<R>*>(a.q), &a.sv->done, &fz);
+        timed(c, kc, 3.0 * vb, [&] { tumor::launch_pcg_update<R>(a, c.st); });
+      },
+      thr2, limit, fixed, pred, conv, bad, rr0);
+  timed(c, kc, 3.0 * vb, [&] { tumor::launch_pcg_xfinal<R>(a, c.st); });
+  return it;
+}
+
+// Elasticity PCG on the two-kernel transforms (tile.hpp): the correction of
+// the FP64 residual r64 (natural order, scaled by `scale`), in tile order.
+// The vectors are r, P.p and x; the arrays between the kernels are A[0..7] with
+// `div`, and B[0..7].  finish() adds the solution to an FP64 vector in natural
+// order.
+template <typename R>
+struct TileSolve {
+  Ctx& c;
+  cplx<R>*r, *p, *x, *div;
+  tumor::SolveScalars* sv;
+
+  explicit TileSolve(Ctx& cc) : c(cc) {
+    PrecBufs<R>& P = pb<R>(c);
+    p = P.p;
+    if (sizeof(R) == 8) {
+      // P.r holds the natural-order residual, free once it has been read; q is
+      // free, and so is the right-hand side b64 (no outer residual follows)
+      r = reinterpret_cast<cplx<R>*>(c.b64);
+      x = P.q;
+      div = P.r;
+      sv = c.sv64;
+    } else {
+      r = P.r;
+      x = P.x;
+      div = P.q;
+      sv = c.sv32;
+    }
+  }
+
+  int run(const cplx<double>* r64, double scale, double thr2, int limit, bool fixed, int pred, bool& conv, bool& bad,
+          double rr0) {
+    PrecBufs<R>& P = pb<R>(c);
+    const double ab = double(c.V) * sizeof(R);  // one array
+    const int kc = kcls<R>(TUMOR_K_KRYLOV64, TUMOR_K_KRYLOV32);
+    timed(c, kc, 3.0 * 8.0 * c.V + 9.0 * ab,
+          [&] { tumor::launch_tile_start<R>(c.n, r64, scale, r, p, x, c.cs, sv, c.partials, c.st); });
+    tumor::TileInvArgs ia;
+    tumor::TileXArgs xa;
+    tumor::TileFwdArgs fa;
+    ia.r = r;
+    ia.p = p;
+    ia.x = x;
+    for (int k = 0; k < 8; ++k) {
+      xa.in[k] = ia.out[k] = P.A[k];
+      fa.in[k] = xa.out[k] = P.B[k];
+    }
+    xa.in[8] = ia.out[8] = div;
+    ia.sv = xa.sv = sv;
+    fa.sv = sv;
+    ia.cs = fa.cs = c.cs;
+    xa.mu = P.mu;
+    xa.lam = P.lam;
+    xa.eta = P.eta;
+    xa.epart = c.dpart;
+    fa.epart = c.dpart;
+    fa.r = r;
+    fa.partials = c.partials;
+    tumor::KrylovArgs ka = kargs<R>(c, 3, x, sv, 0.0, tumor::PREC_ELAST);
+    ka.thr2 = thr2;
+    ka.limit = limit;
+    ka.fixed = fixed ? 1 : 0;
+    return pcg_run(
+        c, sv,
+        [&](int k) {
+          ia.update = k > 0 ? 1 : 0;
+          // (r, p, x in, p, x out or p in) and the nine half arrays out; nine and
+          // three coefficients in, eight out; eight and r in, r out
+          timed(c, kcls<R>(TUMOR_K_TILEINV64, TUMOR_K_TILEINV32), (k > 0 ? 24.0 : 12.0) * ab,
+                [&] { tumor::launch_tile_inv<R>(c.n, ia, P.tw, c.st); });
+          timed(c, kcls<R>(TUMOR_K_TILEX64, TUMOR_K_TILEX32), 20.0 * ab,
+                [&] { tumor::launch_tile_xelast<R>(c.n, xa, P.tw, c.st); });
+          timed(c, kcls<R>(TUMOR_K_TILEFWD64, TUMOR_K_TILEFWD32), 14.0 * ab,
+                [&] { tumor::launch_tile_fwd<R>(c.n, fa, P.tw, c.st); });
+          tumor::launch_fin_update(ka, tumor::tile_fwd_blocks<R>(c.n), c.st);
+        },
+        thr2, limit, fixed, pred, conv, bad, rr0);
+  }
+
+  void finish(cplx<double>* x64, double scale) {
+    timed(c, kcls<R>(TUMOR_K_KRYLOV64, TUMOR_K_KRYLOV32), 3.0 * c.V * (16.0 + 2.0 * sizeof(R)),
+          [&] { tumor::launch_tile_final<R>(c.n, x64, scale, x, p, sv, c.st); });
+  }
+};
 
 // Solve A x = b for a spectral system.  On entry x holds x0 and `resid0`
 // computes r = b - A x0 (and b, norms) into the FP64 vectors.  For the mixed
@@ -811,11 +908,19 @@ SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cp
     return so;
   }
   const int pred = c.pred[which >= 0 ? which : 3];
+  const bool tiled = kind == tumor::PREC_ELAST && tumor::tile_grid(c.n);
+  PrecBufs<double>& P64 = c.p64;
   if (!c.mixed) {
     bool conv = true, bad = false;
     const bool fixed = forced >= 0;
     const int limit = fixed ? forced : c.cfg.max_it;
-    if (limit > 0) so.it = pcg_iterate<double>(c, a, A64, thr2, limit, fixed, pred, 0, conv, bad, rr);
+    if (limit > 0 && tiled) {
+      TileSolve<double> ts(c);
+      so.it = ts.run(P64.r, 1.0, thr2, limit, fixed, pred, conv, bad, rr);
+      ts.finish(x, 1.0);
+    } else if (limit > 0) {
+      so.it = pcg_iterate<double>(c, a, A64, thr2, limit, fixed, pred, 0, conv, bad, rr);
+    }
     so.conv = conv;
     so.bad = bad;
     so.relres = std::sqrt(c.hsv->rr / bb);
@@ -839,7 +944,9 @@ SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cp
     const double rms = std::sqrt(rr / double(cnt));
     const double sc = (rms > 0.0 && std::isfinite(rms)) ? std::ldexp(1.0, -std::ilogb(rms)) : 1.0;
     conv_args.scale32 = sc;
-    timed(c, TUMOR_K_KRYLOV64, ncomp * c.V * (16.0 + 4.0), [&] { tumor::launch_residual<double>(conv_args, P.r, c.st); });
+    if (!tiled)
+      timed(c, TUMOR_K_KRYLOV64, ncomp * c.V * (16.0 + 4.0),
+            [&] { tumor::launch_residual<double>(conv_args, P.r, c.st); });
     const double need = rtol * std::sqrt(bb / rr);
     const double in_rtol = std::max(1e-4, 0.3 * need);
     bool conv = true, bad = false;
@@ -849,7 +956,9 @@ SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cp
     ai.x = P.x;
     const double thr_in = in_rtol * in_rtol * rr * sc * sc;
     int* pin = &c.pred_in[which >= 0 ? which : 3][std::min(so.outer, 2)];
-    inner_it = pcg_iterate<float>(c, ai, A32, thr_in, c.cfg.max_it, false, *pin, 1, conv, bad, rr * sc * sc);
+    TileSolve<float> ts(c);
+    if (tiled) inner_it = ts.run(P64.r, sc, thr_in, c.cfg.max_it, false, *pin, conv, bad, rr * sc * sc);
+    else inner_it = pcg_iterate<float>(c, ai, A32, thr_in, c.cfg.max_it, false, *pin, 1, conv, bad, rr * sc * sc);
     if (conv) *pin = std::max(1, inner_it);
     total += inner_it;
     so.outer++;
@@ -859,7 +968,8 @@ SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cp
       break;
     }
     // x64 += x32 / sc: read x64 and x32, write x64
-    timed(c, TUMOR_K_KRYLOV64, 20.0 * cnt, [&] { tumor::launch_add32to64(x, P.x, 1.0 / sc, cnt, c.st); });
+    if (tiled) ts.finish(x, 1.0 / sc);
+    else timed(c, TUMOR_K_KRYLOV64, 20.0 * cnt, [&] { tumor::launch_add32to64(x, P.x, 1.0 / sc, cnt, c.st); });
     // r64 = b - A64 x64
     A64(x, c.p64.q, nullptr);
     tumor::KrylovArgs ar = a;

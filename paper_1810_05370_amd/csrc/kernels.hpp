@@ -159,6 +159,9 @@ void launch_pcg_start(const KrylovArgs& a, int zero_x, hipStream_t st);
 // (ZPUpdateArgs.x), and launch_pcg_xfinal after the last iteration.
 template <typename R>
 void launch_pcg_update(const KrylovArgs& a, hipStream_t st);
+// The scalars of a finished iteration (count, ||r||^2, convergence, beta)
+// from nb blocks' partials at a.partials.
+void launch_fin_update(const KrylovArgs& a, int nb, hipStream_t st);
 // x += alpha p for the last iteration that ran (none: no-op)
 template <typename R>
 void launch_pcg_xfinal(const KrylovArgs& a, hipStream_t st);

@@ -8,10 +8,12 @@
 #include <algorithm>
 #include <climits>
 #include <cmath>
+#include <stdexcept>
 
 #include "kernels.hpp"
 #include "prec.hpp"
 #include "sl_tile.hpp"
+#include "tile.hpp"
 
 namespace tumor {
 
@@ -1020,6 +1022,10 @@ void launch_pcg_update(const KrylovArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(k_fin_update, dim3(1), dim3(kRedThreads), 0, st, a, nb);
 }
 
+void launch_fin_update(const KrylovArgs& a, int nb, hipStream_t st) {
+  hipLaunchKernelGGL(k_fin_update, dim3(1), dim3(kRedThreads), 0, st, a, nb);
+}
+
 template <typename R>
 void launch_pcg_xfinal(const KrylovArgs& a, hipStream_t st) {
   const long long S = spec_count(a.n);
@@ -1035,6 +1041,135 @@ void launch_precond(const KrylovArgs& a, const void* in, void* out, hipStream_t 
                                                  dim3(256), 0, st, a, ix, static_cast<const cplx<R>*>(in),
                                                  static_cast<cplx<R>*>(out)));
 }
+
+// ------------------------------------- natural order <-> tile order (tile.hpp)
+// A block takes one ky and 16 kz: 16 rows of kx in natural order, runs of
+// 16 KT elements in tile order, turned through LDS so that both sides move
+// whole lines.
+template <int N, int KT>
+struct TurnCfg {
+  static constexpr int C = N / 2, RUN = 16 * KT, NE = 16 * C, PER = NE / kRedThreads, PAD = C + 1;
+  // element k of thread t: natural position (row kz, column kx), tile run position
+  __device__ static int kz(int q) { return q / C; }
+  __device__ static int kx(int q) { return q % C; }
+  // LDS cell of tile-order position q: run (kx / KT), kz, kx % KT
+  __device__ static int cell(int q) { return ((q / KT) % 16) * PAD + (q / RUN) * KT + q % KT; }
+};
+
+template <typename R, int N>
+__global__ void __launch_bounds__(kRedThreads) k_tile_start(const cplx<double>* r64, double scale, cplx<R>* r,
+                                                             cplx<R>* p, cplx<R>* x, const CoefScalars* cs,
+                                                             double* partials) {
+  constexpr int KT = TileCfg<R, N>::KT;
+  using Q = TurnCfg<N, KT>;
+  constexpr long long S = (long long)N * N * Q::C;
+  __shared__ cplx<R> turn[16 * Q::PAD];
+  const int iy = blockIdx.x % N, z0 = (blockIdx.x / N) * 16, ky = wavenum<N>(iy);
+  const ElastMeans em(cs);
+  double acc[1] = {0.0};
+  cplx<R> rv[3][Q::PER], zv[3][Q::PER];
+#pragma unroll
+  for (int k = 0; k < Q::PER; ++k) {
+    const int q = k * kRedThreads + threadIdx.x, iz = z0 + Q::kz(q), kx = Q::kx(q), kz = wavenum<N>(iz);
+    const long long e = ((long long)iz * N + iy) * Q::C + kx;
+    const R wk[3] = {R(kx), R(ky), R(kz)};
+    double ia, f;
+    elast_prec_coefs((double)(kx * kx + ky * ky + kz * kz), em, ia, f);
+    const R ff = R(f), fia = R(ia);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const cplx<double> v = r64[e + c * S];
+      rv[c][k] = {R(scale * v.x), R(scale * v.y)};
+    }
+    const cplx<R> wr = {wk[0] * rv[0][k].x + wk[1] * rv[1][k].x + wk[2] * rv[2][k].x,
+                        wk[0] * rv[0][k].y + wk[1] * rv[1][k].y + wk[2] * rv[2][k].y};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      zv[c][k] = {(rv[c][k].x - ff * wk[c] * wr.x) * fia, (rv[c][k].y - ff * wk[c] * wr.y) * fia};
+      acc[0] += wdot(rv[c][k], zv[c][k], kx);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < Q::PER; ++k) {
+      const int q = k * kRedThreads + threadIdx.x;
+      turn[Q::kz(q) * Q::PAD + Q::kx(q)] = c < 3 ? rv[c % 3][k] : zv[c % 3][k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < Q::PER; ++k) {
+      const int q = k * kRedThreads + threadIdx.x;
+      const long long d = tile_index<N, KT>(z0 + (q / KT) % 16, iy, (q / Q::RUN) * KT + q % KT) + (c % 3) * S;
+      (c < 3 ? r : p)[d] = turn[Q::cell(q)];
+      if (c < 3) x[d] = czero<R>();
+    }
+  }
+  block_store_partials<1>(acc, partials);
+}
+
+template <typename R, int N>
+__global__ void __launch_bounds__(kRedThreads) k_tile_final(cplx<double>* x64, double scale, const cplx<R>* x,
+                                                             const cplx<R>* p, const SolveScalars* sv) {
+  if (sv->it == 0) return;
+  constexpr int KT = TileCfg<R, N>::KT;
+  using Q = TurnCfg<N, KT>;
+  constexpr long long S = (long long)N * N * Q::C;
+  __shared__ cplx<R> turn[16 * Q::PAD];
+  const R alpha = R(sv->alpha);
+  const int iy = blockIdx.x % N, z0 = (blockIdx.x / N) * 16;
+#pragma unroll 1
+  for (int c = 0; c < 3; ++c) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < Q::PER; ++k) {
+      const int q = k * kRedThreads + threadIdx.x;
+      const long long d = tile_index<N, KT>(z0 + (q / KT) % 16, iy, (q / Q::RUN) * KT + q % KT) + c * S;
+      const cplx<R> xv = x[d], pv = p[d];
+      turn[Q::cell(q)] = {xv.x + alpha * pv.x, xv.y + alpha * pv.y};
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < Q::PER; ++k) {
+      const int q = k * kRedThreads + threadIdx.x;
+      const long long e = ((long long)(z0 + Q::kz(q)) * N + iy) * Q::C + Q::kx(q) + c * S;
+      const cplx<R> dv = turn[Q::kz(q) * Q::PAD + Q::kx(q)];
+      cplx<double> v = x64[e];
+      v.x += scale * (double)dv.x;
+      v.y += scale * (double)dv.y;
+      x64[e] = v;
+    }
+  }
+}
+
+template <typename R>
+void launch_tile_start(int n, const void* r64, double scale, void* r, void* p, void* x, const CoefScalars* cs,
+                       SolveScalars* sv, double* partials, hipStream_t st) {
+    constexpr int NN = 256;
+  if (!tile_grid(n)) throw std::logic_error("no tile order on this grid");
+  hipLaunchKernelGGL((k_tile_start<R, NN>), dim3(NN * NN / 16), dim3(kRedThreads), 0, st,
+                                     static_cast<const cplx<double>*>(r64), scale, static_cast<cplx<R>*>(r),
+                                     static_cast<cplx<R>*>(p), static_cast<cplx<R>*>(x), cs, partials);
+  hipLaunchKernelGGL(k_fin_start, dim3(1), dim3(kRedThreads), 0, st, sv, partials, n * n / 16);
+}
+
+template <typename R>
+void launch_tile_final(int n, void* x64, double scale, const void* x, const void* p, const SolveScalars* sv,
+                       hipStream_t st) {
+    constexpr int NN = 256;
+  if (!tile_grid(n)) throw std::logic_error("no tile order on this grid");
+  hipLaunchKernelGGL((k_tile_final<R, NN>), dim3(NN * NN / 16), dim3(kRedThreads), 0, st,
+                                     static_cast<cplx<double>*>(x64), scale, static_cast<const cplx<R>*>(x),
+                                     static_cast<const cplx<R>*>(p), sv);
+}
+
+#define TUMOR_INST_TILE(R)                                                                                     \
+  template void launch_tile_start<R>(int, const void*, double, void*, void*, void*, const CoefScalars*,        \
+                                     SolveScalars*, double*, hipStream_t);                                     \
+  template void launch_tile_final<R>(int, void*, double, const void*, const void*, const SolveScalars*, hipStream_t);
+TUMOR_INST_TILE(double)
+TUMOR_INST_TILE(float)
 
 // ---------------------------------------------- batched independent systems
 // ns one-component systems (PREC_DIFF) sharing an operator: system k's

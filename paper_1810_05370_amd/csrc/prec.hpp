@@ -5,6 +5,21 @@
 
 namespace tumor {
 
+// The elasticity inverse's two coefficients (below), 1/a and c / (a + c |w|^2),
+// from one division and without a branch; m: the coefficient means.
+struct ElastMeans {
+  double eta, mu, c;
+  __device__ __forceinline__ explicit ElastMeans(const CoefScalars* cs)
+      : eta(cs->etabar), mu(cs->mubar), c(cs->lambar + cs->mubar) {}
+};
+__device__ __forceinline__ void elast_prec_coefs(double w2, const ElastMeans& m, double& ia, double& f) {
+  const double a = m.eta + m.mu * w2;
+  const double d = a + m.c * w2;
+  const double inv = 1.0 / (a > 0.0 ? a * d : 1.0);
+  ia = a > 0.0 ? d * inv : 0.0;
+  f = m.c * a * inv;
+}
+
 // Constant-coefficient inverses per Fourier mode (integer wave numbers
 // kx, ky, kz with the Nyquist mode already mapped to 0):
 //   CN diffusion:  1 / (1 + dt/2 mean(K) |w|^2)

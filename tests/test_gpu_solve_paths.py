@@ -1,0 +1,78 @@
+"""The elasticity solve on every grid size its kernels are written for, against
+the oracle: in iteration lockstep in FP64 (a few iterations, where every
+operator, inner product and update counts), and by the FP64 residual of its
+result in the mixed precision.
+
+Tolerances: lockstep differs by rounding alone; a solve of k iterations of an
+operator with condition number about 10 after preconditioning loses a few
+digits of 1e-16, so 1e-11 leaves two orders.  The mixed form promises
+||b - A u|| <= rtol ||b|| in FP64; 1.01 rtol allows for the oracle's own
+rounding of the residual (1e-16 of ||A|| ||u||, under 1e-3 of rtol here).
+"""
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_1810_05370_amd as tm
+import synthetic
+from gpu_common import need_gpu, rel_l2, say
+from oracle import reaction as rx
+from oracle import solvers
+from oracle.spectral import Grid, norm
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(n, precision, rtol, max_it=1000):
+    """A context with tumour, necrosis and a displacement to start from, and the oracle's system."""
+    import torch
+    inp = synthetic.workload_inputs("seeds3_n128", n=n)
+    P = synthetic.params()
+    sim = tm.from_inputs(inp, P, precision=precision, rtol_elast=rtol, max_it=max_it)
+    rng = np.random.default_rng(3)
+    u0 = np.stack([1e-3 * synthetic.random_field(n, 20 + a, 2.0) for a in range(3)])
+    sim.set("u", torch.as_tensor(u0))
+    nec = 0.1 * rng.random((n, n, n))
+    sim.set("n", torch.as_tensor(nec))
+    sim.refresh()
+    p = sim.get("p").cpu().numpy()
+    z = np.zeros_like(p)
+    co = rx.refresh(P, p, z, nec, inp["gm"], inp["wm"], inp["csf"])
+    g = Grid(n)
+    return sim, g, co, rx.elastic_force(g, P["zeta"], p, nec), u0
+
+
+@pytest.mark.parametrize("n", [16, 32, 64, 128, 256])
+def test_elasticity_in_lockstep(n):
+    need_gpu()
+    its = 3 if n == 256 else 6
+    say(f"elasticity lockstep n={n}, {its} iterations")
+    # the iteration cap stops the solve; the last iterate is returned with ENOCONV
+    sim, g, co, force, u0 = _case(n, "fp64", 1e-8, max_it=its)
+    u, it, rr = sim.get("u"), ctypes.c_int32(0), ctypes.c_double(0)
+    code = sim.lib.tumor_solve_elasticity(sim.ctx, None, tm._ptr(u), ctypes.byref(it), ctypes.byref(rr))
+    it, rr = it.value, rr.value
+    assert code == tm.ENOCONV
+    ref, _, rr_ref, _ = solvers.solve_elasticity(g, co["mu"], co["lam"], co["eta"],
+                                                 (co["mubar"], co["lambar"], co["etabar"]), force, u0, 1e-8, 100,
+                                                 fixed_iters=its)
+    err = rel_l2(u.cpu().numpy(), ref)
+    say(f"  relL2 {err:.2e}, residual {rr:.3e} (oracle {rr_ref:.3e})")
+    sim.close()
+    assert it == its
+    assert err < 1e-11
+    assert abs(rr - rr_ref) <= 1e-9 * rr_ref
+
+
+@pytest.mark.parametrize("n", [16, 32, 64, 128, 256])
+def test_mixed_elasticity_meets_its_tolerance(n):
+    need_gpu()
+    say(f"mixed elasticity n={n}")
+    sim, g, co, force, _ = _case(n, "mixed", 1e-8)
+    u, it, rr = sim.solve_elasticity()
+    res = -force - solvers.elasticity_op(g, co["mu"], co["lam"], co["eta"], u.cpu().numpy())
+    rel = norm(res) / norm(force)
+    say(f"  {it} iterations, residual {rr:.3e}, by the oracle {rel:.3e}")
+    sim.close()
+    assert it > 0 and rel <= 1.01e-8 and abs(rel - rr) <= 1e-10
