@@ -10,7 +10,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libtumor.so")
-SOURCES = ["engine.hip", "pointwise.hip", "adjoint.hip", "fft_f64.hip", "fft_f32.hip", "tile_f64.hip", "tile_f32.hip"]
+SOURCES = ["engine.hip", "pointwise.hip", "adjoint.hip", "fft_f64.hip", "fft_f32.hip", "tile_f64.hip", "tile_f32.hip",
+           "plane_f64.hip", "plane_f32.hip"]
 
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIPCC = os.environ.get("HIPCC", os.path.join(ROCM, "bin", "hipcc"))

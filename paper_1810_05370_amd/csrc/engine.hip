@@ -25,6 +25,7 @@
 #include "adjoint.hpp"
 #include "kernels.hpp"
 #include "passes.hpp"
+#include "plane.hpp"
 #include "tile.hpp"
 #include "tumor.h"
 
@@ -148,7 +149,7 @@ struct tumor_ctx {
   cplx<double>* b64;
   PrecBufs<double> p64;
   PrecBufs<float> p32;
-  tumor::SolveScalars* sv64;  // kMaxSys entries (one per system of a batched solve)
+  tumor::SolveScalars* sv64;  // 2 kMaxSys entries (one per system of a batched solve, twice on small grids)
   tumor::SolveScalars* sv32;
   int* bflag;                 // per-system skip flags of the batched FP64 applies
   tumor::CoefScalars* cs;
@@ -316,8 +317,8 @@ void layout(Ctx& c, Carver& cv) {
     for (int k = 0; k < 3; ++k) c.VB[k] = cv.take<double>(V);
     c.gs = cv.take<tumor::GradScalars>(1);
   }
-  c.sv64 = cv.take<tumor::SolveScalars>(tumor::kMaxSys);
-  c.sv32 = cv.take<tumor::SolveScalars>(tumor::kMaxSys);
+  c.sv64 = cv.take<tumor::SolveScalars>(2 * tumor::kMaxSys);
+  c.sv32 = cv.take<tumor::SolveScalars>(2 * tumor::kMaxSys);
   c.bflag = cv.take<int>(4);
   c.cs = cv.take<tumor::CoefScalars>(1);
   c.partials = cv.take<double>((size_t)tumor::kPartialsCount);
@@ -774,7 +775,7 @@ int pcg_iterate(Ctx& c, tumor::KrylovArgs a, Apply apply, double thr2, int limit
   a.limit = limit;
   a.fixed = fixed ? 1 : 0;
   a.dpart = c.dpart;
-  a.dnb = tumor::col_pass_blocks<R>(c.n, 2, a.ncomp);
+  a.dnb = tumor::col_pass_blocks<R>(c.n, 2);
   a.dstride = 1;
   const int kc = kcls<R>(TUMOR_K_KRYLOV64, TUMOR_K_KRYLOV32);
   const double vb = double(a.ncomp) * double(c.V) * sizeof(R);  // one Krylov vector
@@ -877,6 +878,157 @@ struct TileSolve {
   }
 };
 
+// Keeps the timers' batched-apply accounting set for a scope.
+struct BatchScope {
+  Ctx& c;
+  BatchScope(Ctx& cc, int total, int active) : c(cc) {
+    c.bsys_total = total;
+    c.bsys_active = active;
+  }
+  ~BatchScope() {
+    c.bsys_total = 0;
+    c.bsys_active = 0;
+  }
+};
+
+// Krylov solves of small grids (plane.hpp): the elasticity system, or ns
+// diffusion systems at once, as a correction of the FP64 residuals r64
+// (natural order, scaled).  The state alternates between two slots of sv.
+template <typename R>
+struct PlaneSolve {
+  Ctx& c;
+  const bool elast;
+  const int ns;  // states: one, or one per system
+  int launched = 0;
+  tumor::SolveScalars* sv;
+  tumor::PlaneArgs a;
+
+  PlaneSolve(Ctx& cc, bool el, int nsys) : c(cc), elast(el), ns(el ? 1 : nsys) {
+    PrecBufs<R>& P = pb<R>(c);
+    const bool is64 = sizeof(R) == 8;
+    std::memset(&a, 0, sizeof(a));
+    sv = is64 ? c.sv64 : c.sv32;
+    // the half arrays are A[0..7] and B[0]; s, z and the preconditioner the rest.  FP64:
+    // P.r holds the natural-order residual, and the right-hand side b64 is free
+    // (no outer residual follows)
+    for (int k = 0; k < 9; ++k) a.half[k] = k < 8 ? P.A[k] : P.B[0];
+    a.s = P.B[1];
+    a.z = P.B[4];
+    a.prec = P.B[7];
+    a.r = is64 ? reinterpret_cast<cplx<R>*>(c.b64) : P.r;
+    a.p = P.p;
+    a.x = is64 ? P.q : P.x;
+    // the turned coefficients: FP64 in P.r, once the start has read it
+    cplx<R>* turned = is64 ? P.r : P.q;
+    a.mu = turned;
+    a.lam = turned + c.S;
+    a.eta = turned + 2 * c.S;
+    a.cs = c.cs;
+    a.part = c.partials;
+    a.epart = c.dpart;
+    a.h = 0.5 * c.cfg.dt;
+    a.nc = elast ? 3 : nsys;
+  }
+
+  tumor::SolveScalars* slot(int k) const { return sv + (k & 1) * tumor::kMaxSys; }
+
+  // thr2 .. rr0: per state; results in its, conv, bad
+  void run(const cplx<double>* r64, const double (&scale)[tumor::kMaxSys], int active, const double* thr2,
+           const int* limit, const bool* fixed, const int* pred, const double* rr0, int* its, bool* conv, bool* bad) {
+    PrecBufs<R>& P = pb<R>(c);
+    const double ab = double(c.V) * sizeof(R);  // one array
+    const int kc = kcls<R>(TUMOR_K_KRYLOV64, TUMOR_K_KRYLOV32);
+    int most = 0, chunk = 1;
+    bool any_fixed = false;
+    for (int k = 0; k < ns; ++k) {
+      a.thr2[k] = thr2[k];
+      a.limit[k] = limit[k];
+      a.fixed[k] = fixed[k] ? 1 : 0;
+      its[k] = 0;
+      conv[k] = true;
+      bad[k] = false;
+      if (!(active & (1 << k))) continue;
+      // one launch more than the iterations: an iteration's residual is tested
+      // at the start of the next one
+      most = std::max(most, limit[k] + 1);
+      any_fixed = any_fixed || fixed[k];
+      chunk = std::max(chunk, std::min(limit[k], pred[k]) + 1);
+    }
+    if (any_fixed) chunk = std::min(most, 64);
+    launched = 0;
+    tumor::launch_plane_start<R>(c.n, elast, r64, scale, active, a, slot(0), c.st);
+    {
+      const void* in[3] = {P.mu, P.lam, P.eta};
+      void* out[3] = {const_cast<void*>(a.mu), const_cast<void*>(a.lam), const_cast<void*>(a.eta)};
+      if (!elast) {
+        in[0] = P.K;
+        out[0] = out[1];
+      }
+      tumor::launch_plane_coefs<R>(c.n, elast ? 3 : 1, in, out, c.st);
+    }
+    BatchScope scope(c, elast ? 0 : ns, elast ? 0 : __builtin_popcount((unsigned)active));
+    c.batch_ns = elast ? 0 : ns;
+    for (;;) {
+      for (int k = 0; k < chunk && launched < most; ++k, ++launched) {
+        c.cur_tag = launched;
+        a.sv = slot(launched);
+        a.svn = slot(launched + 1);
+        auto stage = [&](int s) { tumor::launch_plane<R>(c.n, elast, s, a, P.tw, c.st); };
+        if (elast) {
+          // r in, z and eight half arrays out; eight and three coefficients in, eight
+          // out; eight, z, s, p, x, r in, s, p, x, r out
+          timed(c, kcls<R>(TUMOR_K_ZINVP64, TUMOR_K_ZINVP32), 14.0 * ab, [&] { stage(0); });
+          timed(c, kcls<R>(TUMOR_K_XELAST64, TUMOR_K_XELAST32), 19.0 * ab, [&] { stage(1); });
+          timed(c, kc, 35.0 * ab, [&] { stage(2); });
+        } else {
+          timed_b(c, kcls<R>(TUMOR_K_ZINVPB64, TUMOR_K_ZINVPB32), 0.0, 5.0 * ab, [&] { stage(0); });
+          timed_b(c, kcls<R>(TUMOR_K_XDIFF64, TUMOR_K_XDIFF32), ab, 6.0 * ab, [&] { stage(1); });
+          timed_b(c, kc, 0.0, 12.0 * ab, [&] { stage(2); });
+        }
+      }
+      c.cur_tag = -1;
+      HIPCHECK(hipGetLastError());
+      HIPCHECK(hipMemcpyAsync(c.hsv, slot(launched), ns * sizeof(tumor::SolveScalars), hipMemcpyDeviceToHost, c.st));
+      HIPCHECK(hipStreamSynchronize(c.st));
+      bool all_done = true;
+      int left = 0;
+      for (int k = 0; k < ns; ++k) {
+        const tumor::SolveScalars& h = c.hsv[k];
+        c.batch_it[k] = (active & (1 << k)) ? h.it : 0;
+        if (!(active & (1 << k)) || h.done) continue;
+        all_done = false;
+        left = std::max(left, std::min(more(h, thr2[k], rr0[k], fixed[k], limit[k]), limit[k] + 1 - h.it));
+      }
+      timers_flush(c, elast ? c.hsv[0].it : 0x7fffffff);
+      if (all_done || launched >= most) break;
+      chunk = std::max(1, std::min(left, any_fixed ? 64 : 32));
+    }
+    c.batch_ns = 0;
+    for (int k = 0; k < ns; ++k) {
+      if (!(active & (1 << k))) continue;
+      its[k] = c.hsv[k].it;
+      conv[k] = c.hsv[k].conv != 0;
+      bad[k] = c.hsv[k].bad != 0;
+    }
+  }
+
+  // launches still needed, from the residual reduction so far
+  static int more(const tumor::SolveScalars& h, double thr2, double rr0, bool fixed, int limit) {
+    if (fixed) return limit + 1 - h.it;
+    // h.rr is the residual before iteration h.it
+    if (rr0 > 0.0 && h.it > 1 && h.rr > thr2 && h.rr < rr0 && std::isfinite(h.rr)) {
+      const double per_it = std::log(h.rr / rr0) / (h.it - 1);
+      const double left = std::log(thr2 / h.rr) / per_it;
+      if (std::isfinite(left)) return std::max(1, std::min(32, (int)std::ceil(left) + 1));
+    }
+    return 4;
+  }
+
+  void finish(cplx<double>* x64, const double (&scale)[tumor::kMaxSys], int active) {
+    tumor::launch_plane_final<R>(c.n, elast, x64, scale, active, a, slot(launched), c.st);
+  }
+};
+
 // Solve A x = b for a spectral system.  On entry x holds x0 and `resid0`
 // computes r = b - A x0 (and b, norms) into the FP64 vectors.  For the mixed
 // precision the FP32 inner PCG corrects x in FP64 outer iterations.
@@ -909,12 +1061,18 @@ SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cp
   }
   const int pred = c.pred[which >= 0 ? which : 3];
   const bool tiled = kind == tumor::PREC_ELAST && tumor::tile_grid(c.n);
+  const bool planes = kind == tumor::PREC_ELAST && tumor::plane_grid(c.n);
+  constexpr double kOnes[tumor::kMaxSys] = {1.0, 1.0, 1.0};
   PrecBufs<double>& P64 = c.p64;
   if (!c.mixed) {
     bool conv = true, bad = false;
     const bool fixed = forced >= 0;
     const int limit = fixed ? forced : c.cfg.max_it;
-    if (limit > 0 && tiled) {
+    if (limit > 0 && planes) {
+      PlaneSolve<double> ps(c, true, 1);
+      ps.run(P64.r, kOnes, 1, &thr2, &limit, &fixed, &pred, &rr, &so.it, &conv, &bad);
+      ps.finish(x, kOnes, 1);
+    } else if (limit > 0 && tiled) {
       TileSolve<double> ts(c);
       so.it = ts.run(P64.r, 1.0, thr2, limit, fixed, pred, conv, bad, rr);
       ts.finish(x, 1.0);
@@ -944,7 +1102,7 @@ SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cp
     const double rms = std::sqrt(rr / double(cnt));
     const double sc = (rms > 0.0 && std::isfinite(rms)) ? std::ldexp(1.0, -std::ilogb(rms)) : 1.0;
     conv_args.scale32 = sc;
-    if (!tiled)
+    if (!tiled && !planes)
       timed(c, TUMOR_K_KRYLOV64, ncomp * c.V * (16.0 + 4.0),
             [&] { tumor::launch_residual<double>(conv_args, P.r, c.st); });
     const double need = rtol * std::sqrt(bb / rr);
@@ -957,7 +1115,12 @@ SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cp
     const double thr_in = in_rtol * in_rtol * rr * sc * sc;
     int* pin = &c.pred_in[which >= 0 ? which : 3][std::min(so.outer, 2)];
     TileSolve<float> ts(c);
-    if (tiled) inner_it = ts.run(P64.r, sc, thr_in, c.cfg.max_it, false, *pin, conv, bad, rr * sc * sc);
+    PlaneSolve<float> ps(c, true, 1);
+    if (planes) {
+      const double scale[tumor::kMaxSys] = {sc, sc, sc}, rr_in = rr * sc * sc;
+      const bool fixed = false;
+      ps.run(P64.r, scale, 1, &thr_in, &c.cfg.max_it, &fixed, pin, &rr_in, &inner_it, &conv, &bad);
+    } else if (tiled) inner_it = ts.run(P64.r, sc, thr_in, c.cfg.max_it, false, *pin, conv, bad, rr * sc * sc);
     else inner_it = pcg_iterate<float>(c, ai, A32, thr_in, c.cfg.max_it, false, *pin, 1, conv, bad, rr * sc * sc);
     if (conv) *pin = std::max(1, inner_it);
     total += inner_it;
@@ -968,7 +1131,9 @@ SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cp
       break;
     }
     // x64 += x32 / sc: read x64 and x32, write x64
-    if (tiled) ts.finish(x, 1.0 / sc);
+    const double inv_sc[tumor::kMaxSys] = {1.0 / sc, 1.0 / sc, 1.0 / sc};
+    if (planes) ps.finish(x, inv_sc, 1);
+    else if (tiled) ts.finish(x, 1.0 / sc);
     else timed(c, TUMOR_K_KRYLOV64, 20.0 * cnt, [&] { tumor::launch_add32to64(x, P.x, 1.0 / sc, cnt, c.st); });
     // r64 = b - A64 x64
     A64(x, c.p64.q, nullptr);
@@ -993,8 +1158,16 @@ SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cp
   return so;
 }
 
+void cn_solve_b(Ctx& c, int ns, const double* const* src, double* const* dst, const int* which, SolveOut* so,
+                bool rhs = false);
+
 // Crank-Nicolson diffusion of the physical field src into dst (may alias).
 SolveOut cn_solve(Ctx& c, const double* src, double* dst, int which) {
+  if (tumor::plane_grid(c.n)) {
+    SolveOut so;
+    cn_solve_b(c, 1, &src, &dst, &which, &so);
+    return so;
+  }
   const double h = 0.5 * c.cfg.dt;
   cplx<double>* x = c.Un;  // free between elasticity solves
   cplx<double>* b = c.b64;
@@ -1050,19 +1223,6 @@ struct BFuse {
   void* x;
   tumor::SolveScalars* sv;  // ns entries
   tumor::PrecConsts pc;
-};
-
-// Keeps the timers' batched-apply accounting set for a scope.
-struct BatchScope {
-  Ctx& c;
-  BatchScope(Ctx& cc, int total, int active) : c(cc) {
-    c.bsys_total = total;
-    c.bsys_active = active;
-  }
-  ~BatchScope() {
-    c.bsys_total = 0;
-    c.bsys_active = 0;
-  }
 };
 
 // out_k = raw * in_k + dcoef * D in_k (spectral) for the ns systems whose
@@ -1163,7 +1323,7 @@ void pcg_iterate_b(Ctx& c, tumor::BatchArgs a, const double* thr2, const int* li
   }
   if (any_fixed) chunk = std::min(lim_max, 64);
   a.dpart = c.dpart;
-  a.dnb = tumor::col_pass_blocks<R>(c.n, 2, 1);
+  a.dnb = tumor::col_pass_blocks<R>(c.n, 2);
   const int kc = kcls<R>(TUMOR_K_KRYLOV64, TUMOR_K_KRYLOV32);
   const double vb = double(c.V) * sizeof(R);  // one system's Krylov vector
   const int nact = __builtin_popcount((unsigned)a.active);
@@ -1226,7 +1386,7 @@ void pcg_iterate_b(Ctx& c, tumor::BatchArgs a, const double* thr2, const int* li
 // (1 - dt/2 D) y_k = src[k] from y_k = 0, and the solutions stay spectral in
 // the blocks of Un (dst unused).
 void cn_solve_b(Ctx& c, int ns, const double* const* src, double* const* dst, const int* which, SolveOut* so,
-                bool rhs = false) {
+                bool rhs) {
   const double h = 0.5 * c.cfg.dt;
   const long long S = c.S;
   const int all = (1 << ns) - 1;
@@ -1236,6 +1396,7 @@ void cn_solve_b(Ctx& c, int ns, const double* const* src, double* const* dst, co
     fwd3<double>(c, src[k], nullptr, rhs ? c.b64 + k * S : x + k * S);
   }
   PrecBufs<double>& P = c.p64;
+  const bool planes = tumor::plane_grid(c.n);
   tumor::BatchArgs a = bargs<double>(c, ns, all, x, c.sv64, h);
   a.b = c.b64;
   const int* flag[tumor::kMaxSys] = {};
@@ -1292,7 +1453,14 @@ void cn_solve_b(Ctx& c, int ns, const double* const* src, double* const* dst, co
     if (active) {
       tumor::BatchArgs ai = a;
       ai.active = active;
-      pcg_iterate_b<double>(c, ai, thr2, limit, fixed, pred, 0, rr, its, conv, bad);
+      if (planes) {
+        const double ones[tumor::kMaxSys] = {1.0, 1.0, 1.0};
+        PlaneSolve<double> ps(c, false, ns);
+        ps.run(P.r, ones, active, thr2, limit, fixed, pred, rr, its, conv, bad);
+        ps.finish(x, ones, active);
+      } else {
+        pcg_iterate_b<double>(c, ai, thr2, limit, fixed, pred, 0, rr, its, conv, bad);
+      }
       for (int k = 0; k < ns; ++k) {
         if (!(active & (1 << k))) continue;
         so[k].it = its[k];
@@ -1332,11 +1500,16 @@ void cn_solve_b(Ctx& c, int ns, const double* const* src, double* const* dst, co
         pred[k] = c.pred_in[which[k]][std::min(so[k].outer, 2)];
         cv.scale32[k] = sc[k];
       }
-      timed(c, TUMOR_K_KRYLOV64, __builtin_popcount((unsigned)active) * c.V * (16.0 + 4.0),
-            [&] { tumor::launch_bresidual<double>(cv, Q.r, c.st); });
-      tumor::BatchArgs ai = a32;
-      ai.active = active;
-      pcg_iterate_b<float>(c, ai, thr_in, limit, fixed, pred, 1, rr_in, its, conv, bad);
+      PlaneSolve<float> ps(c, false, ns);
+      if (planes) {
+        ps.run(P.r, sc, active, thr_in, limit, fixed, pred, rr_in, its, conv, bad);
+      } else {
+        timed(c, TUMOR_K_KRYLOV64, __builtin_popcount((unsigned)active) * c.V * (16.0 + 4.0),
+              [&] { tumor::launch_bresidual<double>(cv, Q.r, c.st); });
+        tumor::BatchArgs ai = a32;
+        ai.active = active;
+        pcg_iterate_b<float>(c, ai, thr_in, limit, fixed, pred, 1, rr_in, its, conv, bad);
+      }
       double inv_sc[tumor::kMaxSys] = {1.0, 1.0, 1.0};
       int stop = 0;
       for (int k = 0; k < ns; ++k) {
@@ -1357,8 +1530,11 @@ void cn_solve_b(Ctx& c, int ns, const double* const* src, double* const* dst, co
       int add = 0;
       for (int k = 0; k < ns; ++k)
         if ((active & (1 << k)) && !so[k].bad) add |= 1 << k;
-      timed_b(c, TUMOR_K_KRYLOV64, 20.0 * cnt * __builtin_popcount((unsigned)add), 0.0,
-              [&] { tumor::launch_badd32to64(x, Q.x, inv_sc, ns, add, cnt, c.st); });
+      if (planes)
+        ps.finish(x, inv_sc, add);
+      else
+        timed_b(c, TUMOR_K_KRYLOV64, 20.0 * cnt * __builtin_popcount((unsigned)add), 0.0,
+                [&] { tumor::launch_badd32to64(x, Q.x, inv_sc, ns, add, cnt, c.st); });
       // r64 = b - A64 x64 for the systems that added a correction
       if (add) {
         apply64(add, x, P.q, 1.0, -h);

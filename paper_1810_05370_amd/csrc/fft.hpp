@@ -150,7 +150,23 @@ __device__ __forceinline__ cplx<R> twiddle(const cplx<R>* __restrict__ tw, int m
   }
 }
 
-template <typename R, int L, bool INV, int TWS, int r, int p, bool LAST, typename View, bool HALF = false>
+// One wave's LDS accesses complete in order; this keeps the compiler from
+// reordering them across an exchange within the wave.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// Synchronisation of an exchange: the block's, or (WAVE: every transform's
+// threads are lanes of one wave) the wave's.
+template <bool WAVE>
+__device__ __forceinline__ void fft_sync() {
+  if constexpr (WAVE) wave_sync();
+  else __syncthreads();
+}
+
+template <typename R, int L, bool INV, int TWS, int r, int p, bool LAST, typename View, bool HALF = false,
+          bool WAVE = false>
 __device__ __forceinline__ void fft_stage(cplx<R> (&v)[8], const View& lds, int t,
                                           const cplx<R>* __restrict__ tw) {
   constexpr int TP = L / 8;
@@ -162,7 +178,7 @@ __device__ __forceinline__ void fft_stage(cplx<R> (&v)[8], const View& lds, int 
 #pragma unroll
     for (int j = 0; j < r; ++j) u[b * r + j] = lds.get(i + j * (L / r));
   }
-  if constexpr (!LAST) __syncthreads();
+  if constexpr (!LAST) fft_sync<WAVE>();
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     const int i = t + TP * b;
@@ -182,27 +198,28 @@ __device__ __forceinline__ void fft_stage(cplx<R> (&v)[8], const View& lds, int 
       for (int m = 0; m < r; ++m) lds.put((i - k) * r + k + m * p, u[b * r + m]);
     }
   }
-  if constexpr (!LAST) __syncthreads();
+  if constexpr (!LAST) fft_sync<WAVE>();
 }
 
 // In-place transform of the 8 register elements (positions t + TP*j).
-// All threads of the block must call it (it synchronises the block).
-template <typename R, int L, bool INV, int TWS, typename View, bool HALF = false>
+// All threads of the block must call it (it synchronises the block, or with
+// WAVE the wave).
+template <typename R, int L, bool INV, int TWS, typename View, bool HALF = false, bool WAVE = false>
 __device__ __forceinline__ void fft_block(cplx<R> (&v)[8], const View& lds, int t,
                                           const cplx<R>* __restrict__ tw) {
   dft8<R, INV>(v);
   if constexpr (Radix<L>::S > 1) {
 #pragma unroll
     for (int m = 0; m < 8; ++m) lds.put(t * 8 + m, v[m]);
-    __syncthreads();
+    fft_sync<WAVE>();
     constexpr int r2 = Radix<L>::r2;
     if constexpr (Radix<L>::S == 2) {
-      fft_stage<R, L, INV, TWS, r2, 8, true, View, HALF>(v, lds, t, tw);
+      fft_stage<R, L, INV, TWS, r2, 8, true, View, HALF, WAVE>(v, lds, t, tw);
     } else {
-      fft_stage<R, L, INV, TWS, r2, 8, false, View, HALF>(v, lds, t, tw);
-      fft_stage<R, L, INV, TWS, Radix<L>::r3, 8 * r2, true, View, HALF>(v, lds, t, tw);
+      fft_stage<R, L, INV, TWS, r2, 8, false, View, HALF, WAVE>(v, lds, t, tw);
+      fft_stage<R, L, INV, TWS, Radix<L>::r3, 8 * r2, true, View, HALF, WAVE>(v, lds, t, tw);
     }
-    __syncthreads();
+    fft_sync<WAVE>();
   }
 }
 

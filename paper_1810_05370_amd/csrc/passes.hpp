@@ -31,6 +31,15 @@ constexpr int kMaxTerms = 3;
 // pass at 64^3 or below has at most 64 column tiles or 256 row waves, far too
 // few to fill 256 CUs, and lasts as long as one block's chain of transforms.
 constexpr int kSplitMaxN = 64;
+// Grids whose elasticity iteration runs on the two-kernel transforms (tile.hpp).
+// At 256^3 it moves 58 arrays instead of 89 (FP32 1.23 -> 1.13 ms, FP64 2.44 ->
+// 2.10).  A 128^3 grid's arrays stay in the 256 MB last-level cache, where the
+// saved passes bring nothing (FP32 0.18 -> 0.19 ms); a 512^3 tile does not fit
+// LDS with 64-byte pieces.
+constexpr bool tile_grid(int n) { return n == 256; }
+// Grids whose Krylov iterations run in three kernels on kx planes (plane.hpp):
+// a plane of 128^2 no longer fits LDS.
+constexpr bool plane_grid(int n) { return n <= 64; }
 
 enum ColSym : int { SYM_ONE = 0, SYM_IW = 1, SYM_RAW = 2 };
 
@@ -179,9 +188,8 @@ template <typename R>
 void launch_xforce(int n, const XForceArgs& a, const void* tw, hipStream_t st);
 template <typename R>
 void launch_xdot(int n, const XDotArgs& a, const void* tw, hipStream_t st);
-// inner-product partials of a column pass along `axis` with nout outputs that
-// share one product
+// blocks of a column pass along `axis` (the count of its inner-product partials)
 template <typename R>
-int col_pass_blocks(int n, int axis, int nout);
+int col_pass_blocks(int n, int axis);
 
 }  // namespace tumor

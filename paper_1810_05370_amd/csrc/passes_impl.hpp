@@ -2,11 +2,16 @@
 #pragma once
 #include <stdexcept>
 #include <string>
+#include <type_traits>
 
 #include "passes.hpp"
 #include "prec.hpp"
 
 namespace tumor {
+
+// Keeps loads on their side of this point: later ones are not hoisted above it
+// (their results would wait in registers), earlier ones not sunk below it.
+__device__ __forceinline__ void hold_loads() { asm volatile("" ::: "memory"); }
 
 // ----------------------------------------------------------------- geometry
 // Column tiles: TC adjacent kxp columns, TP = N/8 threads per column.  SEG
@@ -124,13 +129,7 @@ __global__ void __launch_bounds__((ColCfg<N, R, SEG>::THREADS), ((DOT && sizeof(
   unsigned am = 0;
   for (int o = blockIdx.z; o < prog.nout; o += gridDim.z)
     if (!(prog.oskip[o] && *prog.oskip[o])) am |= 1u << o;
-  if (am == 0) {
-    if constexpr (DOT) {
-      // a layer without outputs still owns a partial
-      if (!prog.dot_nsys && tid == 0) prog.dpart[(long long)blockIdx.z * gridDim.x * gridDim.y + blk] = 0.0;
-    }
-    return;
-  }
+  if (am == 0) return;
   // the active output after o, or -1
   auto next_out = [&](int o) -> int {
     const unsigned rest = am & ~((2u << o) - 1u);
@@ -235,14 +234,13 @@ __global__ void __launch_bounds__((ColCfg<N, R, SEG>::THREADS), ((DOT && sizeof(
     }
   }
   if constexpr (DOT) {
-    static_assert((N / 2 / TC) * N * kDotStride <= kPartialsCount &&
-                      (N / 2 / TC) * N * (N <= kSplitMaxN ? kMaxCol : 1) <= kPartialsCount,
+    static_assert((N / 2 / TC) * N * kDotStride <= kPartialsCount,
                   "the inner-product partials of every block must fit the partials buffer");
     if (!prog.dot_nsys) {
       // Parseval weight: the packed kx = 0 column counts once, the others twice
       const int kxp = bx * TC + col;
       dotacc *= (kxp == 0) ? 1.0 : 2.0;
-      store_dot_partial(dotacc, prog.dpart, 1, 0, (long long)blockIdx.z * gridDim.x * gridDim.y + blk);
+      store_dot_partial(dotacc, prog.dpart, 1, 0, blk);
     }
   }
 }
@@ -272,46 +270,6 @@ __global__ void __launch_bounds__((ColCfg<N, R, 256>::THREADS))
   const cplx<R>* __restrict__ r = static_cast<const cplx<R>*>(a.r);
   cplx<R>* __restrict__ p = static_cast<cplx<R>*>(a.p);
   cplx<R>* __restrict__ x = static_cast<cplx<R>*>(a.x);
-  if constexpr (N <= kSplitMaxN && NC > 1) {
-    // a small grid's layers take one component each (see col_layers): M^-1 r
-    // needs every component of r, but p, x and the outputs only their own
-    const int c = blockIdx.z;
-    cplx<R> pc[8], rr[8][NC], xv[8];
-    // every load first: the stores below may alias them for all the compiler
-    // knows (FP64 at 32^3: 10.7 us with eight round trips to memory one after
-    // another, 8.2 us with one)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const long long idx = base + (long long)(t + TP * j) * astride;
-#pragma unroll
-      for (int b = 0; b < NC; ++b) rr[j][b] = r[b * S + idx];
-      pc[j] = p[c * S + idx];
-      xv[j] = x ? x[c * S + idx] : czero<R>();
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int n = t + TP * j;
-      const long long idx = base + (long long)n * astride;
-      cplx<R> zv[NC];
-      apply_prec<R, NC>(rr[j], zv, kx, ky, wavenum<N>(n), a.cs, a.pc);
-      const cplx<R> zc = c == 0 ? zv[0] : (c == 1 ? zv[1] : zv[2]);
-      const cplx<R> pv = pc[j];
-      if (x) x[c * S + idx] = {xv[j].x + alpha * pv.x, xv[j].y + alpha * pv.y};
-      pc[j] = {zc.x + beta * pv.x, zc.y + beta * pv.y};
-      p[c * S + idx] = pc[j];
-    }
-#pragma unroll
-    for (int d = 0; d < 2; ++d) {
-      cplx<R> acc[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[j] = d ? ciw(pc[j], R(wavenum<N>(t + TP * j))) : pc[j];
-      fft_block<R, N, true, 1>(acc, lds, t, tw);
-      cplx<R>* __restrict__ dst = static_cast<cplx<R>*>(a.out[2 * c + d]);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) dst[base + (long long)(t + TP * j) * astride] = acc[j];
-    }
-    return;
-  }
   cplx<R> pn[NC][8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
@@ -421,18 +379,18 @@ __device__ __forceinline__ cplx<R> c2r_pre(cplx<R> A, cplx<R> B, int k, const cp
 }
 
 // Packed R2C of the row held as v[j] = (x[2p], x[2p+1]), p = t + TP*j.
-template <typename R, int N, bool HALF = false>
+template <typename R, int N, bool HALF = false, bool WAVE = false>
 __device__ __forceinline__ void row_r2c(cplx<R> (&v)[8], const LdsRowView<R>& lds, int t,
                                         const cplx<R>* __restrict__ tw) {
   constexpr int L = N / 2, TP = L / 8;
-  fft_block<R, L, false, 2, LdsRowView<R>, HALF>(v, lds, t, tw);
+  fft_block<R, L, false, 2, LdsRowView<R>, HALF, WAVE>(v, lds, t, tw);
 #pragma unroll
   for (int j = 0; j < 8; ++j) lds.put(t + TP * j, v[j]);
-  __syncthreads();
+  fft_sync<WAVE>();
   cplx<R> zc[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) zc[j] = cconj(lds.get((L - (t + TP * j)) & (L - 1)));
-  __syncthreads();
+  fft_sync<WAVE>();
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const int k = t + TP * j;
@@ -942,14 +900,11 @@ __global__ void __launch_bounds__(RowCfg<N>::THREADS) k_xdot(XDotArgs a, const c
 // that overwrites an input would race with the other layers' reads, so such a
 // program keeps one layer.
 inline int col_layers(int n, const ColProg& prog) {
-  if (n > kSplitMaxN) return 1;
+  if (n > kSplitMaxN || prog.dsv) return 1;
   for (int o = 0; o < prog.nout; ++o)
     for (int q = 0; q < prog.nout; ++q)
       for (int k = 0; k < prog.nterm[q]; ++k)
-        if (prog.out[o] == prog.in[prog.term[q][k].src]) {
-          if (prog.dsv) throw std::logic_error("an inner-product pass must not overwrite its inputs");
-          return 1;
-        }
+        if (prog.out[o] == prog.in[prog.term[q][k].src]) return 1;
   return prog.nout;
 }
 
@@ -981,29 +936,38 @@ void launch_col_pass(int n, int axis, bool inverse, const ColProg& prog, const v
 }
 
 template <typename R>
-int col_pass_blocks(int n, int axis, int nout) {
+int col_pass_blocks(int n, int axis) {
   int nb = 0;
   TUMOR_DISPATCH_N(n, {
     if (col_seg<R>(axis) == 256) nb = (int)((NN / 2) / ColCfg<NN, R, 256>::TC) * NN;
     else nb = (int)((NN / 2) / ColCfg<NN, R, 128>::TC) * NN;
   });
-  return n <= kSplitMaxN ? nb * nout : nb;
+  return nb;
 }
 
+// (smaller grids' Krylov iterations are plane.hpp's, and the elasticity's at
+// 256^3 tile.hpp's)
 template <typename R>
 void launch_zinv_pupdate(int n, int ncomp, const ZPUpdateArgs& a, const void* tw, hipStream_t st) {
   const cplx<R>* twp = static_cast<const cplx<R>*>(tw);
-  TUMOR_DISPATCH_N(n, {
+  auto launch = [&](auto size) {
+    constexpr int NN = decltype(size)::value;
     using Cfg = ColCfg<NN, R, 256>;
     dim3 grid((NN / 2) / Cfg::TC, NN);
-    if (a.nsys > 0)
+    if (a.nsys > 0) {
       hipLaunchKernelGGL((k_zinv_pupdate_b<R, NN>), dim3(grid.x, grid.y, a.nsys), dim3(Cfg::THREADS), 0, st, a, twp);
-    else if (ncomp == 1)
+    } else if (ncomp == 1) {
       hipLaunchKernelGGL((k_zinv_pupdate<R, NN, 1>), grid, dim3(Cfg::THREADS), 0, st, a, twp);
-    else
-      hipLaunchKernelGGL((k_zinv_pupdate<R, NN, 3>), dim3(grid.x, grid.y, NN <= kSplitMaxN ? 3 : 1),
-                         dim3(Cfg::THREADS), 0, st, a, twp);
-  });
+    } else if constexpr (!tile_grid(NN)) {
+      hipLaunchKernelGGL((k_zinv_pupdate<R, NN, 3>), grid, dim3(Cfg::THREADS), 0, st, a, twp);
+    } else {
+      throw std::logic_error("the elasticity iterates in tile order on this grid");
+    }
+  };
+  if (n == 128) launch(std::integral_constant<int, 128>());
+  else if (n == 256) launch(std::integral_constant<int, 256>());
+  else if (n == 512) launch(std::integral_constant<int, 512>());
+  else throw std::runtime_error("no fused first pass at " + std::to_string(n));
 }
 
 template <typename R>

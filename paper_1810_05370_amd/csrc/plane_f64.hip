@@ -1,0 +1,11 @@
+// Small grids' Krylov iterations instantiated for double arithmetic.
+#include "plane_impl.hpp"
+
+namespace tumor {
+template void launch_plane<double>(int, bool, int, const PlaneArgs&, const void*, hipStream_t);
+template void launch_plane_start<double>(int, bool, const void*, const double (&)[kMaxSys], int, const PlaneArgs&,
+                                     SolveScalars*, hipStream_t);
+template void launch_plane_final<double>(int, bool, void*, const double (&)[kMaxSys], int, const PlaneArgs&,
+                                     const SolveScalars*, hipStream_t);
+template void launch_plane_coefs<double>(int, int, const void* const*, void* const*, hipStream_t);
+}  // namespace tumor

@@ -23,12 +23,6 @@
 
 namespace tumor {
 
-// At 256^3 an elasticity iteration moves 58 arrays instead of 89 (FP32 1.23 ->
-// 1.13 ms, FP64 2.44 -> 2.10).  A 128^3 grid's arrays stay in the 256 MB
-// last-level cache, where the saved passes bring nothing (FP32 0.18 -> 0.19 ms);
-// a 512^3 tile does not fit LDS with 64-byte pieces.
-constexpr bool tile_grid(int n) { return n == 256; }
-
 template <typename R, int N>
 struct TileCfg {
   static constexpr int C = N / 2;

@@ -52,18 +52,6 @@ __device__ __forceinline__ cplx<R> r2c_mix(cplx<R> A, cplx<R> B, cplx<R> w, bool
   return {zero ? A.x + A.y : R(0.5) * (s.x + wd.y), zero ? A.x - A.y : R(0.5) * (s.y - wd.x)};
 }
 
-// One wave's LDS accesses complete in order; this keeps the compiler from
-// reordering them across an exchange within the wave.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Keeps later loads from being hoisted above this point (their results would
-// wait in registers).
-__device__ __forceinline__ void hold_loads() { asm volatile("" ::: "memory"); }
-
 // Has v computed by this point (and its operands' registers free).
 __device__ __forceinline__ void pin(double& v) { asm volatile("" : "+v"(v)); }
 
