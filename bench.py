@@ -32,10 +32,10 @@ CLASSES = ("colinv64", "colfwd64", "colinv32", "colfwd32", "colinv32z", "colfwd3
            "zinvp64c1", "zinvp32c1", "zinvpb64", "zinvpb32", "coldot64", "coldot32",
            "tileinv64", "tileinv32", "tilex64", "tilex32", "tilefwd64", "tilefwd32")
 # classes that time exactly one kernel symbol, so that the roofline's kernel can
-# be matched to a rocprofv3 summary line (xother, sl and krylov group several)
-SINGLE_KERNEL = ("colinv64", "colfwd64", "colinv32", "colfwd32", "colinv32z", "colfwd32z", "coldot64",
-                 "coldot32", "xelast64", "xelast32", "xdiff64", "xdiff32", "zinvp64", "zinvp32", "zinvp64c1",
-                 "zinvp32c1", "zinvpb64", "zinvpb32", "tileinv64", "tileinv32", "tilex64", "tilex32", "tilefwd64",
+# be matched to a rocprofv3 summary line (xother, sl, krylov, xdiff and coldot
+# group several)
+SINGLE_KERNEL = ("colinv64", "colfwd64", "colinv32", "colfwd32", "colinv32z", "colfwd32z", "xelast64",
+                 "xelast32", "zinvp64", "zinvp32", "zinvpb64", "zinvpb32", "tileinv64", "tileinv32", "tilex64", "tilex32", "tilefwd64",
                  "tilefwd32", "react")
 
 # Stable windows of the 256^3 forward workloads: (steps from t = 0 before the

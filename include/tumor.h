@@ -341,7 +341,8 @@ int tumor_interp(tumor_ctx* ctx, const double* q, const double* jx, const double
 int tumor_force_iterations(tumor_ctx* ctx, const int32_t* iters);
 
 /* Measurement hook: bracket every launch of one kernel class (each class is
- * one kernel symbol, except XOTHER, SL, KRYLOV64/32) with HIP events
+ * one kernel symbol, except XOTHER, SL, KRYLOV, XDIFF, XELAST and COLDOT, which
+ * group the forms of one step of the work) with HIP events
  * on the context's stream and accumulate launches, elapsed milliseconds and
  * the algorithmic HBM bytes of those launches (each input and output array
  * counted once).  enable = 1 resets and starts, 0 stops.  Reading flushes
@@ -352,11 +353,11 @@ enum {
   TUMOR_K_KRYLOV64, TUMOR_K_KRYLOV32,
   TUMOR_K_ZINVP64, TUMOR_K_ZINVP32,      /* first pass with the fused direction update
                                             (elasticity, 3 components)                 */
-  TUMOR_K_COLDOT64, TUMOR_K_COLDOT32,    /* last pass with the fused inner product      */
+  TUMOR_K_COLDOT64, TUMOR_K_COLDOT32,    /* last pass with the fused residual update     */
   TUMOR_K_COLINV32Z, TUMOR_K_COLFWD32Z,  /* FP32 z passes (COLINV32/COLFWD32: y passes)  */
-  TUMOR_K_ZINVP64_1, TUMOR_K_ZINVP32_1,  /* fused first pass of a one-field CN solve      */
-  TUMOR_K_ZINVPB64, TUMOR_K_ZINVPB32,    /* fused first pass of the batched CN solve of
-                                            i, o and l                                 */
+  TUMOR_K_ZINVP64_1, TUMOR_K_ZINVP32_1,  /* no kernel: a one-field CN solve is a batch    */
+  TUMOR_K_ZINVPB64, TUMOR_K_ZINVPB32,    /* fused first pass of the batched CN solves
+                                            (i, o and l)                                */
   /* the elasticity iteration's two-kernel transforms (n = 256): spectral side
      inverse (with the direction update), x side, spectral side forward (with the
      residual update) */

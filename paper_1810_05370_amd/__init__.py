@@ -44,22 +44,20 @@ KERNEL_CLASSES = {"colinv64": 0, "colfwd64": 1, "colinv32": 2, "colfwd32": 3, "x
                   "colfwd32z": 18, "zinvp64c1": 19, "zinvp32c1": 20, "zinvpb64": 21, "zinvpb32": 22, "tileinv64": 23, "tileinv32": 24,
                   "tilex64": 25, "tilex32": 26, "tilefwd64": 27, "tilefwd32": 28}
 # rocprofv3 kernel names of each class (for cross-checking event timings against traces)
-KERNEL_NAMES = {"colinv64": "k_col_pass<double, {n}, true, false, 256>",
-                "colfwd64": "k_col_pass<double, {n}, false, false, 256>",
-                "colinv32": "k_col_pass<float, {n}, true, false, 128>",
-                "colfwd32": "k_col_pass<float, {n}, false, false, 128>",
-                "colinv32z": "k_col_pass<float, {n}, true, false, 256>",
-                "colfwd32z": "k_col_pass<float, {n}, false, false, 256>",
-                "coldot64": "k_col_pass<double, {n}, false, true, 256>",
-                "coldot32": "k_col_pass<float, {n}, false, true, 256>",
-                "zinvp64": "k_zinv_pupdate<double, {n}, 3>", "zinvp32": "k_zinv_pupdate<float, {n}, 3>",
-                "zinvp64c1": "k_zinv_pupdate<double, {n}, 1>", "zinvp32c1": "k_zinv_pupdate<float, {n}, 1>",
+KERNEL_NAMES = {"colinv64": "k_col_pass<double, {n}, true, 256>",
+                "colfwd64": "k_col_pass<double, {n}, false, 256>",
+                "colinv32": "k_col_pass<float, {n}, true, 128>",
+                "colfwd32": "k_col_pass<float, {n}, false, 128>",
+                "colinv32z": "k_col_pass<float, {n}, true, 256>",
+                "colfwd32z": "k_col_pass<float, {n}, false, 256>",
+                "coldot64": "k_zfwd_update", "coldot32": "k_zfwd_update",
+                "zinvp64": "k_zinv_pupdate<double, {n}>", "zinvp32": "k_zinv_pupdate<float, {n}>",
                 "zinvpb64": "k_zinv_pupdate_b<double, {n}>", "zinvpb32": "k_zinv_pupdate_b<float, {n}>",
                 "xelast64": "k_xelast<double, {n}>", "xelast32": "k_xelast<float, {n}>",
                 "tileinv64": "k_tile_inv<double, {n}>", "tileinv32": "k_tile_inv<float, {n}>",
                 "tilex64": "k_tile_xelast<double, {n}>", "tilex32": "k_tile_xelast<float, {n}>",
                 "tilefwd64": "k_tile_fwd<double, {n}>", "tilefwd32": "k_tile_fwd<float, {n}>",
-                "xdiff64": "k_xdiff<double, {n}>", "xdiff32": "k_xdiff<float, {n}>", "sl": "k_sl",
+                "xdiff64": "k_xdiff", "xdiff32": "k_xdiff", "sl": "k_sl",
                 "react": "k_react"}
 
 

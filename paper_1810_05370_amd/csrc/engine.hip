@@ -154,7 +154,8 @@ struct tumor_ctx {
   int* bflag;                 // per-system skip flags of the batched FP64 applies
   tumor::CoefScalars* cs;
   double* partials;
-  double* dpart;  // inner-product partials of the last pass of a Krylov apply (read by the update)
+  double* dpart;  // parts of <p, A p> from the x pass of a Krylov apply
+  double* esum;   // their totals per system and z plane
   // host side
   tumor::SolveScalars* hsv;  // kMaxSys entries
   tumor::CoefScalars* hcs;
@@ -321,8 +322,12 @@ void layout(Ctx& c, Carver& cv) {
   c.sv32 = cv.take<tumor::SolveScalars>(2 * tumor::kMaxSys);
   c.bflag = cv.take<int>(4);
   c.cs = cv.take<tumor::CoefScalars>(1);
-  c.partials = cv.take<double>((size_t)tumor::kPartialsCount);
-  c.dpart = cv.take<double>((size_t)tumor::kPartialsCount);
+  // per system: two values per tile of a fused last pass; one per row tile, and
+  // the totals of the planes
+  const long long n = c.n;
+  c.partials = cv.take<double>((size_t)std::max<long long>(tumor::kPartialsCount, 2 * tumor::kMaxSys * tumor::max_z_tiles(n)));
+  c.dpart = cv.take<double>((size_t)std::max<long long>(tumor::kPartialsCount, tumor::kMaxSys * tumor::x_tiles(n)));
+  c.esum = cv.take<double>((size_t)tumor::kMaxSys * n);
 }
 
 size_t workspace_size(const tumor_config& cfg) {
@@ -362,6 +367,15 @@ struct Prog {
     int q = 0;
     for (const ColTerm& t : terms) p.term[o][q++] = t;
     p.nterm[o] = q;
+    return *this;
+  }
+  // the totals of <p, A p> per plane (ColProg.esum)
+  Prog& energies(double* esum, const double* epart, const double* ppart, double escale, int nes) {
+    p.esum = esum;
+    p.epart = epart;
+    p.ppart = ppart;
+    p.escale = escale;
+    p.nes = nes;
     return *this;
   }
   Prog& skip(const int* s) {
@@ -436,10 +450,11 @@ struct DotProg {
   }
 };
 
-// Krylov work fused into an operator apply (see ZPUpdateArgs / ColProg.dsv).
+// Krylov work fused into the first and last pass of the elasticity's apply
+// (ZPUpdateArgs, ZUpdateArgs): with it, no A p is stored.
 struct Fuse {
   bool pupdate;  // first pass: x += alpha p, p = M^-1 r + beta p (in place) before transforming p
-  const void* r;
+  void* r;
   void* x;
   tumor::SolveScalars* sv;
   tumor::PrecConsts pc;
@@ -452,23 +467,12 @@ void colp(Ctx& c, int axis, bool inv, const Prog& pr) {
     for (int q = 0; q < pr.p.nterm[o]; ++q) used[pr.p.term[o][q].src] = true;
   int nin = 0;
   for (int k = 0; k < tumor::kMaxCol; ++k) nin += used[k] ? 1 : 0;
-  // each array once: a dot operand that is also an input is not counted again
-  int ndot = 0;
-  if (pr.p.dsv)
-    for (int o = 0; o < pr.p.nout; ++o) {
-      const void* d = pr.p.dotp[o];
-      bool seen = d == nullptr;
-      for (int k = 0; k < tumor::kMaxCol && !seen; ++k) seen = used[k] && pr.p.in[k] == d;
-      for (int q = 0; q < o && !seen; ++q) seen = pr.p.dotp[q] == d;
-      ndot += seen ? 0 : 1;
-    }
-  const double bytes = double(nin + pr.p.nout + ndot) * double(c.V) * sizeof(R);
+  const double bytes = double(nin + pr.p.nout) * double(c.V) * sizeof(R);
   // FP32 y and z passes are separate kernel instances (segment widths differ),
   // so they are timed as separate classes; every class is one kernel symbol
   const bool z32 = sizeof(R) == 4 && axis == 2;
   const int cls = inv ? (z32 ? TUMOR_K_COLINV32Z : kcls<R>(TUMOR_K_COLINV64, TUMOR_K_COLINV32))
-                      : (pr.p.dsv ? kcls<R>(TUMOR_K_COLDOT64, TUMOR_K_COLDOT32)
-                                  : (z32 ? TUMOR_K_COLFWD32Z : kcls<R>(TUMOR_K_COLFWD64, TUMOR_K_COLFWD32)));
+                      : (z32 ? TUMOR_K_COLFWD32Z : kcls<R>(TUMOR_K_COLFWD64, TUMOR_K_COLFWD32));
   timed(c, cls, bytes,
         [&] { tumor::launch_col_pass<R>(c.n, axis, inv, pr.p, pb<R>(c).tw, c.st); });
 }
@@ -499,36 +503,11 @@ void inv3(Ctx& c, const cplx<R>* in, R* out, double scale, int d = -1) {
   timed(c, TUMOR_K_XOTHER, 2.0 * c.V * sizeof(R), [&] { tumor::launch_xinv<R>(c.n, to_x(x.p, scale), P.tw, c.st); });
 }
 
-// Fused first pass: p = M^-1 r + beta p, then the z-inverse transforms of p
-// and i w_z p per component into outs[2a], outs[2a+1].
-template <typename R>
-void zinv_pupdate(Ctx& c, int ncomp, const Fuse& f, cplx<R>* p, void* const* outs) {
-  tumor::ZPUpdateArgs za;
-  std::memset(&za, 0, sizeof(za));
-  za.r = f.r;
-  za.p = p;
-  za.x = f.x;
-  for (int k = 0; k < 2 * ncomp; ++k) za.out[k] = outs[k];
-  za.sv = f.sv;
-  za.cs = c.cs;
-  za.pc = f.pc;
-  // reads r, p, x; writes p, x and the two transformed outputs
-  const int cls = ncomp == 3 ? kcls<R>(TUMOR_K_ZINVP64, TUMOR_K_ZINVP32) : kcls<R>(TUMOR_K_ZINVP64_1, TUMOR_K_ZINVP32_1);
-  timed(c, cls, 7.0 * ncomp * double(c.V) * sizeof(R),
-        [&] { tumor::launch_zinv_pupdate<R>(c.n, ncomp, za, pb<R>(c).tw, c.st); });
-}
-
 // out = raw * in + dcoef * D in (spectral), D c = div(K grad c).
 template <typename R>
-void diff_apply(Ctx& c, const cplx<R>* in, cplx<R>* out, double raw, double dcoef, const int* skip,
-                const Fuse* fz = nullptr) {
+void diff_apply(Ctx& c, const cplx<R>* in, cplx<R>* out, double raw, double dcoef, const int* skip) {
   PrecBufs<R>& P = pb<R>(c);
-  if (fz && fz->pupdate) {
-    void* outs[2] = {P.A[0], P.A[1]};
-    zinv_pupdate<R>(c, 1, *fz, const_cast<cplx<R>*>(in), outs);
-  } else {
-    colp<R>(c, 2, true, Prog().in(0, in).out(P.A[0], {T1(0)}).out(P.A[1], {TW(0)}).skip(skip));
-  }
+  colp<R>(c, 2, true, Prog().in(0, in).out(P.A[0], {T1(0)}).out(P.A[1], {TW(0)}).skip(skip));
   colp<R>(c, 1, true,
           Prog().in(0, P.A[0]).in(1, P.A[1]).out(P.B[0], {T1(0)}).out(P.B[1], {TW(0)}).out(P.B[2], {T1(1)}).skip(
               skip));
@@ -549,14 +528,8 @@ void diff_apply(Ctx& c, const cplx<R>* in, cplx<R>* out, double raw, double dcoe
           Prog().in(0, P.A[0]).in(1, P.A[1]).in(2, P.A[2]).out(P.B[0], {T1(0), TW(1)}).out(P.B[1], {T1(2)}).skip(skip));
   Prog z;
   z.in(0, P.B[0]).in(1, P.B[1]).in(2, in).skip(skip);
-  // the untransformed term last: the inner-product pass takes p from it
   if (raw != 0.0) z.out(out, {T1(0, dcoef), TW(1, dcoef), TR(2, raw)});
   else z.out(out, {T1(0, dcoef), TW(1, dcoef)});
-  if (fz) {
-    z.p.dotp[0] = in;
-    z.p.dsv = fz->sv;
-    z.p.dpart = c.dpart;
-  }
   colp<R>(c, 2, false, z);
 }
 
@@ -567,9 +540,23 @@ void elast_apply(Ctx& c, const cplx<R>* in, cplx<R>* out, const int* skip, const
   const long long S = c.S;
   auto** A = P.A;
   auto** B = P.B;
+  const double ab = double(c.V) * sizeof(R);  // one array
   if (fz && fz->pupdate) {
-    void* outs[6] = {A[0], A[3], A[1], A[4], A[2], A[5]};
-    zinv_pupdate<R>(c, 3, *fz, const_cast<cplx<R>*>(in), outs);
+    // reads r, p, x; writes p, x and the six transformed outputs
+    tumor::ZPUpdateArgs za;
+    std::memset(&za, 0, sizeof(za));
+    za.r = fz->r;
+    za.p = const_cast<cplx<R>*>(in);
+    za.x = fz->x;
+    for (int k = 0; k < 3; ++k) {
+      za.out[2 * k] = A[k];
+      za.out[2 * k + 1] = A[3 + k];
+    }
+    za.sv = fz->sv;
+    za.cs = c.cs;
+    za.pc = fz->pc;
+    timed(c, kcls<R>(TUMOR_K_ZINVP64, TUMOR_K_ZINVP32), 21.0 * ab,
+          [&] { tumor::launch_zinv_pupdate<R>(c.n, za, P.tw, c.st); });
   } else
   colp<R>(c, 2, true,
           Prog()
@@ -605,6 +592,7 @@ void elast_apply(Ctx& c, const cplx<R>* in, cplx<R>* out, const int* skip, const
   xa.lam = P.lam;
   xa.eta = P.eta;
   xa.skip = skip;
+  xa.epart = fz ? c.dpart : nullptr;
   timed(c, kcls<R>(TUMOR_K_XELAST64, TUMOR_K_XELAST32), 19.0 * c.V * sizeof(R),
         [&] { tumor::launch_xelast<R>(c.n, xa, P.tw, c.st); });
   Prog yf;
@@ -616,18 +604,27 @@ void elast_apply(Ctx& c, const cplx<R>* in, cplx<R>* out, const int* skip, const
       .out(B[4], {T1(5)})
       .out(B[5], {T1(7)})
       .skip(skip);
+  if (fz) yf.energies(c.esum, c.dpart, nullptr, 1.0, 1);
   colp<R>(c, 1, false, yf);
+  if (fz) {
+    tumor::ZUpdateArgs ua;
+    std::memset(&ua, 0, sizeof(ua));
+    for (int k = 0; k < 6; ++k) ua.in[k] = B[k];
+    ua.r = fz->r;
+    ua.sv = fz->sv;
+    ua.cs = c.cs;
+    ua.esum = c.esum;
+    ua.partials = c.partials;
+    timed(c, kcls<R>(TUMOR_K_COLDOT64, TUMOR_K_COLDOT32), 12.0 * ab,
+          [&] { tumor::launch_zfwd_update<R>(c.n, ua, P.tw, c.st); });
+    return;
+  }
   Prog zf;
   for (int k = 0; k < 6; ++k) zf.in(k, B[k]);
   zf.out(out, {T1(0), TW(3, -1.0)})
       .out(out + S, {T1(1), TW(4, -1.0)})
       .out(out + 2 * S, {T1(2), TW(5, -1.0)})
       .skip(skip);
-  if (fz) {
-    for (int k = 0; k < 3; ++k) zf.p.dotp[k] = in + k * S;
-    zf.p.dsv = fz->sv;
-    zf.p.dpart = c.dpart;
-  }
   colp<R>(c, 2, false, zf);
 }
 
@@ -774,20 +771,17 @@ int pcg_iterate(Ctx& c, tumor::KrylovArgs a, Apply apply, double thr2, int limit
   a.thr2 = thr2;
   a.limit = limit;
   a.fixed = fixed ? 1 : 0;
-  a.dpart = c.dpart;
-  a.dnb = tumor::col_pass_blocks<R>(c.n, 2);
-  a.dstride = 1;
   const int kc = kcls<R>(TUMOR_K_KRYLOV64, TUMOR_K_KRYLOV32);
   const double vb = double(a.ncomp) * double(c.V) * sizeof(R);  // one Krylov vector
   timed(c, kc, (zero_x ? 3.0 : 2.0) * vb, [&] { tumor::launch_pcg_start<R>(a, zero_x, c.st); });
-  // iteration k: (p = M^-1 r + beta p fused into the first pass for k > 0),
-  // q = A p with alpha = rho / <p, q> fused into the last pass, then x, r
+  // iteration k: p = M^-1 r + beta p in the first pass (k > 0), A p, alpha and the
+  // update of r in the last
   const int it = pcg_run(
       c, a.sv,
       [&](int k) {
         Fuse fz{k > 0, a.r, a.x, a.sv, a.pc};
         apply(static_cast<const cplx<R>*>(a.p), static_cast<cplx<R>*>(a.q), &a.sv->done, &fz);
-        timed(c, kc, 3.0 * vb, [&] { tumor::launch_pcg_update<R>(a, c.st); });
+        tumor::launch_fin_update(a, tumor::z_tiles<R>(c.n), c.st);
       },
       thr2, limit, fixed, pred, conv, bad, rr0);
   timed(c, kc, 3.0 * vb, [&] { tumor::launch_pcg_xfinal<R>(a, c.st); });
@@ -1158,35 +1152,6 @@ SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cp
   return so;
 }
 
-void cn_solve_b(Ctx& c, int ns, const double* const* src, double* const* dst, const int* which, SolveOut* so,
-                bool rhs = false);
-
-// Crank-Nicolson diffusion of the physical field src into dst (may alias).
-SolveOut cn_solve(Ctx& c, const double* src, double* dst, int which) {
-  if (tumor::plane_grid(c.n)) {
-    SolveOut so;
-    cn_solve_b(c, 1, &src, &dst, &which, &so);
-    return so;
-  }
-  const double h = 0.5 * c.cfg.dt;
-  cplx<double>* x = c.Un;  // free between elasticity solves
-  cplx<double>* b = c.b64;
-  fwd3<double>(c, src, nullptr, x);
-  auto A64 = [&](const cplx<double>* p, cplx<double>* q, const int* skip, const Fuse* fz = nullptr) {
-      diff_apply<double>(c, p, q, 1.0, -h, skip, fz);
-    };
-  auto A32 = [&](const cplx<float>* p, cplx<float>* q, const int* skip, const Fuse* fz = nullptr) {
-      diff_apply<float>(c, p, q, 1.0, -h, skip, fz);
-    };
-  auto r0 = [&](tumor::KrylovArgs& a) {
-    diff_apply<double>(c, x, c.p64.q, 0.0, 1.0, nullptr);
-    timed(c, TUMOR_K_KRYLOV64, 4.0 * c.V * 8.0, [&] { tumor::launch_cn_residual<double>(a, x, c.p64.q, c.st); });
-  };
-  SolveOut so = solve_system(c, 1, tumor::PREC_DIFF, h, x, b, c.cfg.rtol_diff, which, A64, A32, r0);
-  inv3<double>(c, x, dst, 1.0 / (double)c.V);
-  return so;
-}
-
 // ------------------------------------------------ batched CN solves (i, o, l)
 // The Crank-Nicolson systems of the species share the operator (1 - dt/2 D_K)
 // and its preconditioner, so they are solved as one Krylov iteration over ns
@@ -1216,10 +1181,10 @@ tumor::BatchArgs bargs(Ctx& c, int ns, int active, cplx<R>* x, tumor::SolveScala
   return a;
 }
 
-// Krylov work fused into a batched apply (see ZPUpdateArgs.nsys, ColProg.dot_nsys).
+// Krylov work fused into a batched apply (ZPUpdateArgs, ZUpdateArgs).
 struct BFuse {
-  bool pupdate;
-  const void* r;
+  bool first;  // p is transformed as it is
+  void* r;
   void* x;
   tumor::SolveScalars* sv;  // ns entries
   tumor::PrecConsts pc;
@@ -1239,7 +1204,7 @@ void diff_apply_b(Ctx& c, int ns, const cplx<R>* in, cplx<R>* out, double raw, d
     buf[8 + k] = P.B[k];
   }
   const long long S = c.S;
-  if (fz && fz->pupdate) {
+  if (fz) {
     tumor::ZPUpdateArgs za;
     std::memset(&za, 0, sizeof(za));
     za.r = fz->r;
@@ -1250,8 +1215,10 @@ void diff_apply_b(Ctx& c, int ns, const cplx<R>* in, cplx<R>* out, double raw, d
     za.cs = c.cs;
     za.pc = fz->pc;
     za.nsys = ns;
-    timed(c, kcls<R>(TUMOR_K_ZINVPB64, TUMOR_K_ZINVPB32), 7.0 * ns * double(c.V) * sizeof(R),
-          [&] { tumor::launch_zinv_pupdate<R>(c.n, 1, za, P.tw, c.st); });
+    za.ppart = c.partials;
+    za.first = fz->first ? 1 : 0;
+    timed(c, kcls<R>(TUMOR_K_ZINVPB64, TUMOR_K_ZINVPB32), (fz->first ? 3.0 : 7.0) * ns * double(c.V) * sizeof(R),
+          [&] { tumor::launch_zinv_pupdate<R>(c.n, za, P.tw, c.st); });
   } else {
     Prog z;
     for (int k = 0; k < ns; ++k) z.in(k, in + k * S).out(buf[2 * k], {T1(k)}, skip[k]).out(buf[2 * k + 1], {TW(k)}, skip[k]);
@@ -1271,6 +1238,7 @@ void diff_apply_b(Ctx& c, int ns, const cplx<R>* in, cplx<R>* out, double raw, d
   for (int k = 0; k < ns; ++k) xa.skip[k] = skip[k];
   xa.K = P.K;
   xa.ns = ns;
+  xa.epart = fz ? c.dpart : nullptr;
   // K once, then three rows in and three out per system
   timed_b(c, kcls<R>(TUMOR_K_XDIFF64, TUMOR_K_XDIFF32), double(c.V) * sizeof(R), 6.0 * double(c.V) * sizeof(R),
           [&] { tumor::launch_xdiff<R>(c.n, xa, P.tw, c.st); });
@@ -1281,21 +1249,31 @@ void diff_apply_b(Ctx& c, int ns, const cplx<R>* in, cplx<R>* out, double raw, d
         .in(3 * k + 2, buf[8 + 3 * k])
         .out(buf[2 * k], {T1(3 * k), TW(3 * k + 1)}, skip[k])
         .out(buf[2 * k + 1], {T1(3 * k + 2)}, skip[k]);
+  if (fz) yf.energies(c.esum, c.dpart, c.partials, fz->pc.h, ns);
   colp<R>(c, 1, false, yf);
+  if (fz) {
+    tumor::ZUpdateArgs ua;
+    std::memset(&ua, 0, sizeof(ua));
+    for (int k = 0; k < 2 * ns; ++k) ua.in[k] = buf[k];
+    ua.r = fz->r;
+    ua.p = in;
+    ua.sv = fz->sv;
+    ua.cs = c.cs;
+    ua.esum = c.esum;
+    ua.partials = c.partials;
+    ua.pc = fz->pc;
+    ua.nsys = ns;
+    timed_b(c, kcls<R>(TUMOR_K_COLDOT64, TUMOR_K_COLDOT32), 0.0, 5.0 * double(c.V) * sizeof(R),
+            [&] { tumor::launch_zfwd_update<R>(c.n, ua, P.tw, c.st); });
+    return;
+  }
   Prog zf;
   for (int k = 0; k < ns; ++k) {
     zf.in(3 * k, buf[2 * k]).in(3 * k + 1, buf[2 * k + 1]).in(3 * k + 2, in + k * S);
-    // the untransformed term last: the inner-product pass takes p from it
     if (raw != 0.0)
       zf.out(out + k * S, {T1(3 * k, dcoef), TW(3 * k + 1, dcoef), TR(3 * k + 2, raw)}, skip[k]);
     else
       zf.out(out + k * S, {T1(3 * k, dcoef), TW(3 * k + 1, dcoef)}, skip[k]);
-  }
-  if (fz) {
-    for (int k = 0; k < ns; ++k) zf.p.dotp[k] = in + k * S;
-    zf.p.dsv = fz->sv;
-    zf.p.dpart = c.dpart;
-    zf.p.dot_nsys = ns;
   }
   colp<R>(c, 2, false, zf);
 }
@@ -1322,8 +1300,6 @@ void pcg_iterate_b(Ctx& c, tumor::BatchArgs a, const double* thr2, const int* li
     chunk = std::max(chunk, std::min(limit[k], pred[k] + 1));
   }
   if (any_fixed) chunk = std::min(lim_max, 64);
-  a.dpart = c.dpart;
-  a.dnb = tumor::col_pass_blocks<R>(c.n, 2);
   const int kc = kcls<R>(TUMOR_K_KRYLOV64, TUMOR_K_KRYLOV32);
   const double vb = double(c.V) * sizeof(R);  // one system's Krylov vector
   const int nact = __builtin_popcount((unsigned)a.active);
@@ -1337,10 +1313,10 @@ void pcg_iterate_b(Ctx& c, tumor::BatchArgs a, const double* thr2, const int* li
   for (;;) {
     for (int i = 0; i < chunk && launched < lim_max; ++i, ++launched) {
       c.cur_tag = launched;
-      BFuse fz{launched > 0, a.r, a.x, a.sv, a.pc};
+      BFuse fz{launched == 0, a.r, a.x, a.sv, a.pc};
       diff_apply_b<R>(c, ns, static_cast<const cplx<R>*>(a.p), static_cast<cplx<R>*>(a.q), 1.0, -a.pc.h, skip,
                       &fz);
-      timed_b(c, kc, 0.0, 3.0 * vb, [&] { tumor::launch_bpcg_update<R>(a, c.st); });
+      tumor::launch_bfin_update(a, tumor::z_tiles<R>(c.n), c.st);
     }
     c.cur_tag = -1;
     HIPCHECK(hipGetLastError());
@@ -1386,7 +1362,7 @@ void pcg_iterate_b(Ctx& c, tumor::BatchArgs a, const double* thr2, const int* li
 // (1 - dt/2 D) y_k = src[k] from y_k = 0, and the solutions stay spectral in
 // the blocks of Un (dst unused).
 void cn_solve_b(Ctx& c, int ns, const double* const* src, double* const* dst, const int* which, SolveOut* so,
-                bool rhs) {
+                bool rhs = false) {
   const double h = 0.5 * c.cfg.dt;
   const long long S = c.S;
   const int all = (1 << ns) - 1;
@@ -1791,7 +1767,10 @@ void do_step(Ctx& c, tumor_step_stats* stats, int& status) {
   substep_mark(c, 1);
   if (c.single) {
     // Single-species model: CN diffusion of c, then its reaction and the refresh.
-    sd[0] = cn_solve(c, c.G[P], c.Rdd[0], 0);
+    const double* const src[1] = {c.G[P]};
+    double* const dst[1] = {c.Rdd[0]};
+    const int which[1] = {0};
+    cn_solve_b(c, 1, src, dst, which, sd);
     substep_mark(c, 2);
     const double* in[9] = {c.G[P], c.G[P], c.Rdd[0], c.G[N], c.G[G], c.G[W], c.F[O], c.F[L], c.G[F]};
     double* out[8] = {c.F[P], c.F[I], c.F[N], c.F[G], c.F[W], c.F[O], c.F[L], c.F[F]};
@@ -2001,26 +1980,16 @@ void zero(Ctx& c, double* p, long long count) {
   HIPCHECK(hipMemsetAsync(p, 0, count * sizeof(double), c.st));
 }
 
-// Adjoint solve A y = rhs (physical rhs, ncomp blocks) with x0 = 0; y stays
-// spectral in c.Un.  kind: diffusion (A = 1 - dt/2 D_K) or elasticity.
-SolveOut adjoint_solve(Ctx& c, int ncomp, const double* rhs, int which) {
-  for (int k = 0; k < ncomp; ++k) fwd3<double>(c, rhs + k * c.V, nullptr, c.b64 + k * c.S);
+// Adjoint elasticity solve A y = rhs (three physical blocks) with x0 = 0; y stays
+// spectral in c.Un.
+SolveOut adjoint_solve(Ctx& c, const double* rhs, int which) {
+  for (int k = 0; k < 3; ++k) fwd3<double>(c, rhs + k * c.V, nullptr, c.b64 + k * c.S);
   cplx<double>* x = c.Un;
-  HIPCHECK(hipMemsetAsync(x, 0, ncomp * c.S * sizeof(cplx<double>), c.st));
-  const double h = 0.5 * c.cfg.dt;
+  HIPCHECK(hipMemsetAsync(x, 0, 3 * c.S * sizeof(cplx<double>), c.st));
   auto r0 = [&](tumor::KrylovArgs& a) {
     a.ax = nullptr;
     tumor::launch_residual<double>(a, nullptr, c.st);
   };
-  if (ncomp == 1) {
-    auto A64 = [&](const cplx<double>* p, cplx<double>* q, const int* skip, const Fuse* fz = nullptr) {
-      diff_apply<double>(c, p, q, 1.0, -h, skip, fz);
-    };
-    auto A32 = [&](const cplx<float>* p, cplx<float>* q, const int* skip, const Fuse* fz = nullptr) {
-      diff_apply<float>(c, p, q, 1.0, -h, skip, fz);
-    };
-    return solve_system(c, 1, tumor::PREC_DIFF, h, x, c.b64, c.cfg.rtol_diff, which, A64, A32, r0);
-  }
   auto A64 = [&](const cplx<double>* p, cplx<double>* q, const int* skip, const Fuse* fz = nullptr) {
     elast_apply<double>(c, p, q, skip, fz);
   };
@@ -2162,7 +2131,7 @@ void adjoint_core(Ctx& c, const double* x0, double* adj, int m, double* grad) {
   PrecBufs<double>& PB = c.p64;
   // ---- S6 elasticity and force, S5 mixture
   if (c.flags & TUMOR_F_ELASTICITY) {
-    adjoint_solve(c, 3, Lm[8], 7);  // y (spectral) in Un
+    adjoint_solve(c, Lm[8], 7);  // y (spectral) in Un
     elast_sens(c);
     force_adj(c);
     tumor::launch_axpy(V, 1.0, c.TB, Lm[P], c.st);

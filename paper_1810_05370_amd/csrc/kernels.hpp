@@ -11,10 +11,7 @@ namespace tumor {
 constexpr int kRedThreads = 256;
 constexpr int kRedBlocksMax = 1024;
 constexpr int kPartialsPerBlock = 16;
-// The partials buffer: kRedBlocksMax blocks of kPartialsPerBlock for the
-// reductions, or up to kPartialsCount / kDotStride blocks of an FFT pass with
-// one inner-product partial per batched system.
-constexpr int kDotStride = 4;
+// The least size of a partials buffer.
 constexpr int kPartialsCount = 65536;
 static_assert(kPartialsCount >= kRedBlocksMax * kPartialsPerBlock, "partials buffer");
 // Independent systems of a batched solve (the CN solves of i, o and l).
@@ -137,30 +134,18 @@ struct KrylovArgs {
   int limit;     // iteration limit (max_it or a forced count)
   int fixed;     // 1: ignore convergence, stop at `limit`
   double scale32;  // launch_residual: r32 = float(scale32 * r), a power of two
-  // launch_pcg_update: the inner-product pass's block partials of <p, q>
-  // (dnb blocks, dstride apart); every block of the update totals them
-  // itself (same order as a one-block kernel) to get alpha = rho / <p, q>
-  const double* dpart;
-  int dnb, dstride;
 };
 
 // r = b - ax (ax nullable: r = b); bb, rr -> sv.  Optionally r32 = float(r).
 template <typename R>
 void launch_residual(const KrylovArgs& a, void* r32, hipStream_t st);
-// CN start from c (= x0) and D c: b = c + h Dc, r = b - (c - h Dc); bb, rr -> sv.
-template <typename R>
-void launch_cn_residual(const KrylovArgs& a, const void* c, const void* dc, hipStream_t st);
 // p = M^-1 r; rho = <r, M^-1 r>; it = 0; done = 0.  zero_x: x = 0 as well.
 template <typename R>
 void launch_pcg_start(const KrylovArgs& a, int zero_x, hipStream_t st);
-// alpha = rho / <p, q> (from the partials at a.dpart), r -= alpha q,
-// convergence test, beta.  x += alpha p is deferred: the fused
-// p-update pass of the next iteration applies it before replacing p
-// (ZPUpdateArgs.x), and launch_pcg_xfinal after the last iteration.
-template <typename R>
-void launch_pcg_update(const KrylovArgs& a, hipStream_t st);
 // The scalars of a finished iteration (count, ||r||^2, convergence, beta)
-// from nb blocks' partials at a.partials.
+// from nb tiles' partials, two each, at a.partials.  x += alpha p is deferred: the
+// fused first pass of the next iteration applies it before replacing p
+// (ZPUpdateArgs.x), and launch_pcg_xfinal after the last iteration.
 void launch_fin_update(const KrylovArgs& a, int nb, hipStream_t st);
 // x += alpha p for the last iteration that ran (none: no-op)
 template <typename R>
@@ -186,9 +171,6 @@ struct BatchArgs {
   int limit[kMaxSys];
   int fixed[kMaxSys];
   double scale32[kMaxSys];  // launch_bresidual: r32 = float(scale32 * r)
-  // launch_bpcg_update: system k's <p, q> partials at dpart[block * kDotStride + k], dnb blocks
-  const double* dpart;
-  int dnb;
 };
 template <typename R>
 void launch_bresidual(const BatchArgs& a, void* r32, hipStream_t st);
@@ -196,8 +178,8 @@ template <typename R>
 void launch_bcn_residual(const BatchArgs& a, const void* c, const void* dc, hipStream_t st);
 template <typename R>
 void launch_bpcg_start(const BatchArgs& a, int zero_x, hipStream_t st);
-template <typename R>
-void launch_bpcg_update(const BatchArgs& a, hipStream_t st);
+// launch_fin_update per system (system s's partials from 2 nb s on)
+void launch_bfin_update(const BatchArgs& a, int nb, hipStream_t st);
 template <typename R>
 void launch_bpcg_xfinal(const BatchArgs& a, hipStream_t st);
 // flags[k] = 0 for the systems in mask, 1 for the others (k < ns)

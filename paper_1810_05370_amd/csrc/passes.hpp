@@ -62,15 +62,15 @@ struct ColProg {
   // per output: if non-null and *oskip[o] != 0, output o is not computed
   // (a converged system of a batched solve)
   const int* oskip[kMaxCol];
-  // Optional fused Krylov inner product of a forward z pass: with dsv set,
-  // each block stores its partial of sum_o <dotp[o], out[o]> (Parseval-
-  // weighted) in dpart[block]; the PCG update that follows totals them
-  // (col_pass_blocks blocks).  With dot_nsys > 0, output o belongs to system
-  // o of a batched solve: its partial goes to dpart[block * kDotStride + o].
-  const void* dotp[kMaxCol];
-  SolveScalars* dsv;
-  double* dpart;
-  int dot_nsys;
+  // Optional, in the forward y pass of a Krylov apply: the totals per z plane
+  // and system of <p, A p>, from the x pass's energies and, with ppart, the
+  // first pass's squared norms of p: esum[system * N + plane] =
+  // escale * (the plane's epart) + (as many ppart).
+  double* esum;
+  const double* epart;
+  const double* ppart;
+  double escale;
+  int nes;  // systems
 };
 
 // First (inverse z) pass of a Krylov operator apply with the direction update
@@ -85,6 +85,27 @@ struct ZPUpdateArgs {
   void* out[6];
   SolveScalars* sv;
   const CoefScalars* cs;
+  PrecConsts pc;
+  int nsys;
+  // nsys > 0: each block's part of ||p||^2 at ppart[block * nsys + system]; `first`
+  // transforms p as it is (the start has made it)
+  double* ppart;
+  int first;
+};
+
+// Last (forward z) pass of a Krylov operator apply with the residual update
+// fused in: q = A p is formed in registers, alpha = rho / <p, q> comes from the N
+// plane totals at esum, r -= alpha q in place; each block stores its parts of
+// ||r||^2 and <r, M^-1 r> at partials[2 * (system * tiles + tile)].  Elasticity (nsys 0): q_c = F in[c] - i w_z F in[3 + c]; system
+// s of a batch: q = p - h (F in[2s] + i w_z F in[2s + 1]).
+struct ZUpdateArgs {
+  const void* in[6];
+  void* r;
+  const void* p;  // batch
+  SolveScalars* sv;
+  const CoefScalars* cs;
+  const double* esum;
+  double* partials;
   PrecConsts pc;
   int nsys;
 };
@@ -114,6 +135,7 @@ struct XElastArgs {
   const void* lam;
   const void* eta;
   const int* skip;
+  double* epart;  // nullable: each row tile's part of <p, A p> (its energy times N^3)
 };
 
 // Diffusion x pass for ns fields (systems) sharing K.  Inputs per field s:
@@ -126,6 +148,7 @@ struct XDiffArgs {
   const void* K;
   const int* skip[3];
   int ns;
+  double* epart;  // nullable: epart[tile * ns + s] = the row tile's part of -<c, D c>
 };
 
 // Force x pass.  Inputs: T, dy t, dz t (packed rows of tau = p + n).
@@ -175,7 +198,7 @@ template <typename R>
 void launch_col_pass(int n, int axis /*1 = y, 2 = z*/, bool inverse, const ColProg& prog,
                      const void* tw, hipStream_t st);
 template <typename R>
-void launch_zinv_pupdate(int n, int ncomp, const ZPUpdateArgs& a, const void* tw, hipStream_t st);
+void launch_zinv_pupdate(int n, const ZPUpdateArgs& a, const void* tw, hipStream_t st);
 template <typename R>
 void launch_xinv(int n, const XProg& prog, const void* tw, hipStream_t st);
 template <typename R>
@@ -188,8 +211,14 @@ template <typename R>
 void launch_xforce(int n, const XForceArgs& a, const void* tw, hipStream_t st);
 template <typename R>
 void launch_xdot(int n, const XDotArgs& a, const void* tw, hipStream_t st);
-// blocks of a column pass along `axis` (the count of its inner-product partials)
 template <typename R>
-int col_pass_blocks(int n, int axis);
+void launch_zfwd_update(int n, const ZUpdateArgs& a, const void* tw, hipStream_t st);
+// tiles of a fused first or last pass (the count of its partials)
+template <typename R>
+int z_tiles(int n);
+// row tiles of an x pass (RowCfg: one wave of 64 threads, n / 16 to a row)
+constexpr long long x_tiles(long long n) { return n * n * n / 1024; }
+// no grid has more tiles of a fused first or last pass
+constexpr long long max_z_tiles(long long n) { return n * n / 16; }
 
 }  // namespace tumor

@@ -13,6 +13,15 @@ namespace tumor {
 // (their results would wait in registers), earlier ones not sunk below it.
 __device__ __forceinline__ void hold_loads() { asm volatile("" ::: "memory"); }
 
+// Has v computed by this point (and its operands' registers free).
+__device__ __forceinline__ void pin(double& v) { asm volatile("" : "+v"(v)); }
+
+// The same value, not known to be computable before this point.
+__device__ __forceinline__ int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 // ----------------------------------------------------------------- geometry
 // Column tiles: TC adjacent kxp columns, TP = N/8 threads per column.  SEG
 // is the width in bytes of the contiguous segment a tile reads per position
@@ -37,6 +46,10 @@ struct ColCfg {
 // Segment width of a column pass: 256 bytes for z passes and for FP64.
 template <typename R>
 constexpr int col_seg(int axis) { return (axis == 2 || sizeof(R) == 8) ? 256 : 128; }
+
+// Tiles of the fused first and last passes of a Krylov apply.
+template <int N, typename R>
+using ZCfg = ColCfg<N, R, 256>;
 
 // Copy the twiddle table into LDS (all threads), so butterflies read LDS.
 template <typename R, int N>
@@ -63,35 +76,59 @@ __device__ __forceinline__ int xwave(int k) {  // x wave number of packed index 
   return k;                                    // k = 0 carries both kx = 0 and kx = N/2: w = 0
 }
 
-// Block sum of v stored as this block's partial of an inner product (plain
-// store in slot blk, by default the workgroup's linear index; the PCG update
-// that follows the pass totals the partials).
 __device__ __forceinline__ double wave_sum_f(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
 }
 
-__device__ void store_dot_partial(double v, double* part, int stride = 1, int slot = 0, long long blk = -1) {
-  __shared__ double sh[16];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-  v = wave_sum_f(v);
-  __syncthreads();  // a previous call's total has read sh
-  if (lane == 0) sh[wv] = v;
+// Totals of a block of TH threads (fixed order), valid in every thread; sh:
+// NV * TH / 64 doubles of LDS that nothing else is using.
+template <int NV, int TH>
+__device__ __forceinline__ void block_totals(double (&v)[NV], double* sh) {
+  constexpr int NW = TH / 64;
+  static_assert(TH % 64 == 0, "whole waves");
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   __syncthreads();
-  if (threadIdx.x == 0) {
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const double s = wave_sum_f(v[i]);
+    if (lane == 0) sh[i * NW + wv] = s;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
     double s = 0.0;
-    for (int w = 0; w < nw; ++w) s += sh[w];
-    if (blk < 0) blk = (long long)blockIdx.y * gridDim.x + blockIdx.x;
-    part[blk * stride + slot] = s;
+    for (int k = 0; k < NW; ++k) s += sh[i * NW + k];
+    v[i] = s;
   }
 }
 
+// alpha = rho / <p, A p> from nb parts (every block totals them in the same
+// order); the lead block publishes it, or the breakdown (alpha 0: nothing left
+// for the deferred x update to add).
+template <int TH>
+__device__ __forceinline__ bool block_alpha(SolveScalars* sv, const double* part, int nb, bool lead, double* sh,
+                                            double& alpha) {
+  double tot[1] = {0.0};
+  for (int k = threadIdx.x; k < nb; k += TH) tot[0] += part[k];
+  block_totals<1, TH>(tot, sh);
+  const bool ok = isfinite(tot[0]) && tot[0] > 0.0;
+  alpha = ok ? sv->rho / tot[0] : 0.0;
+  if (lead && threadIdx.x == 0) {
+    sv->pq = tot[0];
+    sv->alpha = alpha;
+    if (!ok) {
+      sv->bad = 1;
+      sv->done = 1;
+    }
+  }
+  return ok;
+}
+
 // ---------------------------------------------------------------- col pass
-// The FP32 inner-product variant is held to 128 VGPRs (4 waves per SIMD),
-// the occupancy of the other FP32 passes.
-template <typename R, int N, bool INV, bool DOT, int SEG>
-__global__ void __launch_bounds__((ColCfg<N, R, SEG>::THREADS), ((DOT && sizeof(R) == 4) ? 4 : 1))
+template <typename R, int N, bool INV, int SEG>
+__global__ void __launch_bounds__((ColCfg<N, R, SEG>::THREADS))
     k_col_pass(ColProg prog, long long fstride, long long astride, const cplx<R>* __restrict__ twg) {
   if (prog.skip && *prog.skip) return;
   using Cfg = ColCfg<N, R, SEG>;
@@ -113,10 +150,8 @@ __global__ void __launch_bounds__((ColCfg<N, R, SEG>::THREADS), ((DOT && sizeof(
   const int lin = blockIdx.y * gx + blockIdx.x;
   const int bx = ypass ? (lin >> 3) % gx : (int)blockIdx.x;
   const int by = ypass ? ((lin >> 3) / gx) * 8 + (lin & 7) : (int)blockIdx.y;
-  const long long blk = (long long)by * gx + bx;  // the tile's inner-product slot
   const long long base = (long long)by * fstride + (long long)bx * TC + col;
   const LdsView<R> lds{sbuf + col, TC, 1};
-  double dotacc = 0.0;
   // Software pipelining: the input column of the next FFT job is loaded into
   // `nxt` before the current job's FFT, whose barriers wait on LDS only.
   auto load_col = [&](cplx<R>(&dst)[8], int src) {
@@ -136,9 +171,22 @@ __global__ void __launch_bounds__((ColCfg<N, R, SEG>::THREADS), ((DOT && sizeof(
     return rest ? __builtin_ctz(rest) : -1;
   };
   cplx<R> nxt[8];
-  cplx<R> pdot[8];
-  (void)pdot;
   load_col(nxt, prog.term[__builtin_ctz(am)][0].src);
+  if constexpr (!INV && !plane_grid(N)) {
+    // one wave of a plane's first tile totals the plane's parts of <p, A p>
+    if (prog.esum && bx == 0 && tid < 64) {
+      constexpr int NE = N / RowCfg<N>::RW, NP = (N / 2) / ZCfg<N, R>::TC;
+      for (int s = 0; s < prog.nes; ++s) {
+        double e = 0.0;
+        for (int i = tid; i < NE; i += 64) e += prog.epart[((long long)by * NE + i) * prog.nes + s];
+        e *= prog.escale;
+        if (prog.ppart)
+          for (int i = tid; i < NP; i += 64) e += prog.ppart[((long long)by * NP + i) * prog.nes + s];
+        e = wave_sum_f(e);
+        if (tid == 0) prog.esum[s * N + by] = e;
+      }
+    }
+  }
   for (int o = __builtin_ctz(am); o >= 0; o = next_out(o)) {
     const int on = next_out(o);
     cplx<R> acc[8];
@@ -177,12 +225,7 @@ __global__ void __launch_bounds__((ColCfg<N, R, SEG>::THREADS), ((DOT && sizeof(
     } else {
 #pragma unroll
       for (int j = 0; j < 8; ++j) acc[j] = czero<R>();
-      // inner-product pass: a last untransformed term read from the operand p
-      // already holds p at the output positions, so it is taken after the loop
-      const ColTerm last = prog.term[o][nt - 1];
-      const bool rawlast = DOT && last.sym == SYM_RAW && prog.in[last.src] == prog.dotp[o];
-      const int nloop = rawlast ? nt - 1 : nt;
-      for (int q = 0; q < nloop; ++q) {
+      for (int q = 0; q < nt; ++q) {
         const ColTerm tm = prog.term[o][q];
         const R cf = R(tm.coef);
         cplx<R> tmp[8];
@@ -199,57 +242,19 @@ __global__ void __launch_bounds__((ColCfg<N, R, SEG>::THREADS), ((DOT && sizeof(
           acc[j].y += cf * v.y;
         }
       }
-      if constexpr (DOT) {
-        if (rawlast) {
-          const R cf = R(last.coef);
-#pragma unroll
-          for (int j = 0; j < 8; ++j) pdot[j] = nxt[j];
-          if (on >= 0) load_col(nxt, prog.term[on][0].src);
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            acc[j].x += cf * pdot[j].x;
-            acc[j].y += cf * pdot[j].y;
-          }
-        } else {
-          // the operand loaded after the transforms: held across them it
-          // would push the pass into spills
-          const cplx<R>* __restrict__ pp = static_cast<const cplx<R>*>(prog.dotp[o]);
-#pragma unroll
-          for (int j = 0; j < 8; ++j) pdot[j] = pp[base + (long long)(t + TP * j) * astride];
-        }
-      }
     }
     cplx<R>* __restrict__ dst = static_cast<cplx<R>*>(prog.out[o]);
 #pragma unroll
     for (int j = 0; j < 8; ++j) dst[base + (long long)(t + TP * j) * astride] = acc[j];
-    if constexpr (DOT) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) dotacc += (double)pdot[j].x * (double)acc[j].x + (double)pdot[j].y * (double)acc[j].y;
-      if (prog.dot_nsys) {
-        // output o is system o's direction: its own partial
-        const int kxp = bx * TC + col;
-        store_dot_partial(dotacc * ((kxp == 0) ? 1.0 : 2.0), prog.dpart, kDotStride, o, blk);
-        dotacc = 0.0;
-      }
-    }
-  }
-  if constexpr (DOT) {
-    static_assert((N / 2 / TC) * N * kDotStride <= kPartialsCount,
-                  "the inner-product partials of every block must fit the partials buffer");
-    if (!prog.dot_nsys) {
-      // Parseval weight: the packed kx = 0 column counts once, the others twice
-      const int kxp = bx * TC + col;
-      dotacc *= (kxp == 0) ? 1.0 : 2.0;
-      store_dot_partial(dotacc, prog.dpart, 1, 0, blk);
-    }
   }
 }
 
-template <typename R, int N, int NC>
-__global__ void __launch_bounds__((ColCfg<N, R, 256>::THREADS))
+template <typename R, int N>
+__global__ void __launch_bounds__((ZCfg<N, R>::THREADS))
     k_zinv_pupdate(ZPUpdateArgs a, const cplx<R>* __restrict__ twg) {
+  constexpr int NC = 3;
   if (a.sv->done) return;
-  using Cfg = ColCfg<N, R, 256>;
+  using Cfg = ZCfg<N, R>;
   constexpr int TP = Cfg::TP, TC = Cfg::TC;
   constexpr long long C = N / 2;
   constexpr long long S = (long long)N * N * C;
@@ -311,12 +316,12 @@ __global__ void __launch_bounds__((ColCfg<N, R, 256>::THREADS))
 // batched solve): blockIdx.z is the system, whose scalars are a.sv[z]; the
 // blocks of a system whose solve is done exit at once.
 template <typename R, int N>
-__global__ void __launch_bounds__((ColCfg<N, R, 256>::THREADS))
+__global__ void __launch_bounds__((ZCfg<N, R>::THREADS))
     k_zinv_pupdate_b(ZPUpdateArgs a, const cplx<R>* __restrict__ twg) {
   const int sy = blockIdx.z;
   const SolveScalars* sv = a.sv + sy;
   if (sv->done) return;
-  using Cfg = ColCfg<N, R, 256>;
+  using Cfg = ZCfg<N, R>;
   constexpr int TP = Cfg::TP, TC = Cfg::TC;
   constexpr long long C = N / 2;
   constexpr long long S = (long long)N * N * C;
@@ -342,18 +347,27 @@ __global__ void __launch_bounds__((ColCfg<N, R, 256>::THREADS))
   for (int j = 0; j < 8; ++j) {
     const int n = t + TP * j;
     const long long idx = sy * S + base + (long long)n * astride;
-    cplx<R> rv[1] = {r[idx]}, zv[1];
-    apply_prec<R, 1>(rv, zv, kx, ky, wavenum<N>(n), a.cs, a.pc);
     const cplx<R> pv = p[idx];
-    if (x) {
+    pn[j] = pv;
+    if (!a.first) {
+      cplx<R> rv[1] = {r[idx]}, zv[1];
+      apply_prec<R, 1>(rv, zv, kx, ky, wavenum<N>(n), a.cs, a.pc);
       cplx<R> xv = x[idx];
       xv.x += alpha * pv.x;
       xv.y += alpha * pv.y;
       x[idx] = xv;
+      pn[j] = {zv[0].x + beta * pv.x, zv[0].y + beta * pv.y};
+      p[idx] = pn[j];
     }
-    pn[j] = {zv[0].x + beta * pv.x, zv[0].y + beta * pv.y};
-    p[idx] = pn[j];
   }
+  double pp[1] = {0.0};
+#pragma unroll
+  for (int j = 0; j < 8; ++j) pp[0] += (double)pn[j].x * (double)pn[j].x + (double)pn[j].y * (double)pn[j].y;
+  // Parseval weight: the packed kx = 0 column counts once, the others twice
+  pp[0] *= kx == 0 ? 1.0 : 2.0;
+  __shared__ double sh[Cfg::THREADS / 64];
+  block_totals<1, Cfg::THREADS>(pp, sh);
+  if (tid == 0) a.ppart[((long long)blockIdx.y * gridDim.x + blockIdx.x) * a.nsys + sy] = pp[0];
 #pragma unroll
   for (int d = 0; d < 2; ++d) {
     cplx<R> acc[8];
@@ -363,6 +377,174 @@ __global__ void __launch_bounds__((ColCfg<N, R, 256>::THREADS))
     cplx<R>* __restrict__ dst = static_cast<cplx<R>*>(a.out[2 * sy + d]);
 #pragma unroll
     for (int j = 0; j < 8; ++j) dst[base + (long long)(t + TP * j) * astride] = acc[j];
+  }
+}
+
+// Last pass of the elasticity's apply with the residual update (ZUpdateArgs).
+// Bound by memory: 12 arrays, where a pass that stores q = A p and an update
+// that reads it move 18.  With <p, A p> from the x pass's energies, alpha is
+// known before this pass.  At 128^3 44 us in FP64 (4.6 TB/s) for 39 and 36 of
+// the two, 26 us in FP32 for 24 and 24; the energies cost the x pass 4 us.
+// Tiles of 128-byte segments, twice as many, are no faster (44 and 25 us).
+template <typename R, int N>
+__global__ void __launch_bounds__((ZCfg<N, R>::THREADS))
+    k_zfwd_update(ZUpdateArgs a, const cplx<R>* __restrict__ twg) {
+  if (a.sv->done) return;
+  using Cfg = ZCfg<N, R>;
+  constexpr int TP = Cfg::TP, TC = Cfg::TC;
+  constexpr long long C = N / 2;
+  constexpr long long S = (long long)N * N * C;
+  constexpr long long astride = (long long)N * C;
+  __shared__ cplx<R> sbuf[Cfg::LDS];
+  __shared__ cplx<R> stw[N];
+  __shared__ double sh[2 * (Cfg::THREADS / 64)];
+  static_assert((C / TC) * N <= max_z_tiles(N) && (long long)N * N / RowCfg<N>::RW == x_tiles(N), "partials");
+  const int tid = threadIdx.x;
+  const int col = tid % TC;
+  const int t = tid / TC;
+  const int kx = blockIdx.x * TC + col;
+  const int ky = wavenum<N>(blockIdx.y);
+  // block-uniform bases and a 32-bit lane offset, as in k_xelast
+  const int lane = (int)blockIdx.y * (int)C + kx + t * (int)astride;
+  const LdsView<R> lds{sbuf + col, TC, 1};
+  auto load_col = [&](cplx<R>(&v)[8], const void* src) {
+    const cplx<R>* __restrict__ sp = static_cast<const cplx<R>*>(src);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = (sp + TP * j * astride)[lane];
+  };
+  // a block of 1024 threads has no registers to load ahead into
+  constexpr bool AHEAD = Cfg::THREADS <= 512;
+  cplx<R> nxt[8];
+  load_col(nxt, a.in[0]);
+  hold_loads();
+  stage_twiddles<R, N>(stw, twg);
+  const cplx<R>* tw = stw;
+  double al;
+  if (!block_alpha<Cfg::THREADS>(a.sv, a.esum, N, blockIdx.x == 0 && blockIdx.y == 0, sh, al)) return;
+  const R alpha = R(al);
+  cplx<R>* r = static_cast<cplx<R>*>(a.r);
+  double acc[2] = {0.0, 0.0};
+#pragma unroll 1
+  for (int c = 0; c < 3; ++c) {
+    cplx<R> u[8], w[8], rv[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) u[j] = nxt[j];
+    if constexpr (AHEAD) load_col(w, a.in[3 + c]);
+    fft_block<R, N, false, 1>(u, lds, t, tw);
+    if constexpr (!AHEAD) load_col(w, a.in[3 + c]);
+    auto load_r = [&] {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) rv[j] = (r + c * S + TP * j * astride)[lane];
+    };
+    if constexpr (AHEAD) {
+      load_r();
+      if (c < 2) load_col(nxt, a.in[c + 1]);
+    }
+    fft_block<R, N, false, 1>(w, lds, t, tw);
+    if constexpr (!AHEAD) load_r();
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const cplx<R> q = csub(u[j], ciw(w[j], R(wavenum<N>(t + TP * j))));
+      rv[j].x -= alpha * q.x;
+      rv[j].y -= alpha * q.y;
+      (r + c * S + TP * j * astride)[lane] = rv[j];
+      acc[0] += (double)rv[j].x * (double)rv[j].x + (double)rv[j].y * (double)rv[j].y;
+    }
+    if (!AHEAD && c < 2) load_col(nxt, a.in[c + 1]);
+  }
+  // <r, M^-1 r>: the three components come back from memory (held, they would
+  // take 96 registers in FP64)
+  const ElastMeans em(a.cs);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    if (j % 4 == 0) hold_loads();
+    cplx<R> rv[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) rv[c] = (r + c * S + TP * j * astride)[lane];
+    const int kz = wavenum<N>(t + TP * j), kxo = opaque(kx);
+    double ia, f;
+    elast_prec_coefs((double)(kxo * kxo + ky * ky + kz * kz), em, ia, f);
+    const R wk[3] = {R(kx), R(ky), R(kz)}, ff = R(f), fia = R(ia);
+    const cplx<R> wr = {wk[0] * rv[0].x + wk[1] * rv[1].x + wk[2] * rv[2].x,
+                        wk[0] * rv[0].y + wk[1] * rv[1].y + wk[2] * rv[2].y};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const R zx = (rv[c].x - ff * wk[c] * wr.x) * fia, zy = (rv[c].y - ff * wk[c] * wr.y) * fia;
+      acc[1] += (double)rv[c].x * (double)zx + (double)rv[c].y * (double)zy;
+    }
+    pin(acc[1]);
+  }
+  acc[0] *= kx == 0 ? 1.0 : 2.0;
+  acc[1] *= kx == 0 ? 1.0 : 2.0;
+  block_totals<2, Cfg::THREADS>(acc, sh);
+  if (tid == 0) {
+    double* part = a.partials + 2 * ((long long)blockIdx.y * gridDim.x + blockIdx.x);
+    part[0] = acc[0];
+    part[1] = acc[1];
+  }
+}
+
+// The same for a.nsys independent diffusion systems (blockIdx.z): 5 arrays a
+// system for 7.  At 256^3, three systems: FP64 333 us for 430, FP32 171 for 215.
+template <typename R, int N>
+__global__ void __launch_bounds__((ZCfg<N, R>::THREADS))
+    k_zfwd_update_b(ZUpdateArgs a, const cplx<R>* __restrict__ twg) {
+  const int sy = blockIdx.z;
+  SolveScalars* sv = a.sv + sy;
+  if (sv->done) return;
+  using Cfg = ZCfg<N, R>;
+  constexpr int TP = Cfg::TP, TC = Cfg::TC;
+  constexpr long long C = N / 2;
+  constexpr long long S = (long long)N * N * C;
+  constexpr long long astride = (long long)N * C;
+  __shared__ cplx<R> sbuf[Cfg::LDS];
+  __shared__ cplx<R> stw[N];
+  __shared__ double sh[2 * (Cfg::THREADS / 64)];
+  const int tid = threadIdx.x;
+  const int col = tid % TC;
+  const int t = tid / TC;
+  const int kx = blockIdx.x * TC + col;
+  const int ky = wavenum<N>(blockIdx.y);
+  const long long base = (long long)blockIdx.y * C + kx;
+  const LdsView<R> lds{sbuf + col, TC, 1};
+  auto load_col = [&](cplx<R>(&v)[8], const void* src) {
+    const cplx<R>* __restrict__ sp = static_cast<const cplx<R>*>(src);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = sp[base + (long long)(t + TP * j) * astride];
+  };
+  cplx<R>* __restrict__ r = static_cast<cplx<R>*>(a.r) + sy * S;
+  cplx<R> u[8], w[8], pv[8], rv[8];
+  load_col(u, a.in[2 * sy]);
+  load_col(w, a.in[2 * sy + 1]);
+  hold_loads();
+  stage_twiddles<R, N>(stw, twg);
+  const cplx<R>* tw = stw;
+  double al;
+  if (!block_alpha<Cfg::THREADS>(sv, a.esum + sy * N, N, blockIdx.x == 0 && blockIdx.y == 0, sh, al)) return;
+  const R alpha = R(al), h = R(a.pc.h);
+  fft_block<R, N, false, 1>(u, lds, t, tw);
+  load_col(pv, static_cast<const cplx<R>*>(a.p) + sy * S);
+  load_col(rv, r);
+  fft_block<R, N, false, 1>(w, lds, t, tw);
+  double acc[2] = {0.0, 0.0};
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int kz = wavenum<N>(t + TP * j);
+    const cplx<R> d = cadd(u[j], ciw(w[j], R(kz)));
+    const cplx<R> q = {pv[j].x - h * d.x, pv[j].y - h * d.y};
+    cplx<R> rn[1] = {{rv[j].x - alpha * q.x, rv[j].y - alpha * q.y}}, zv[1];
+    r[base + (long long)(t + TP * j) * astride] = rn[0];
+    apply_prec<R, 1>(rn, zv, kx, ky, kz, a.cs, a.pc);
+    acc[0] += (double)rn[0].x * (double)rn[0].x + (double)rn[0].y * (double)rn[0].y;
+    acc[1] += (double)rn[0].x * (double)zv[0].x + (double)rn[0].y * (double)zv[0].y;
+  }
+  acc[0] *= kx == 0 ? 1.0 : 2.0;
+  acc[1] *= kx == 0 ? 1.0 : 2.0;
+  block_totals<2, Cfg::THREADS>(acc, sh);
+  if (tid == 0) {
+    double* part = a.partials + 2 * (((long long)sy * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x);
+    part[0] = acc[0];
+    part[1] = acc[1];
   }
 }
 
@@ -562,9 +744,9 @@ __global__ void __launch_bounds__(RowCfg<N>::THREADS) k_xfwd(XProg prog, const c
   }
 }
 
-template <typename R, int N>
-__global__ void __launch_bounds__(RowCfg<N>::THREADS, (sizeof(R) == 4 ? 3 : 2))
-    k_xelast(XElastArgs a, const cplx<R>* __restrict__ twg) {
+// EN: also the energy sum of each row tile (XElastArgs.epart).
+template <typename R, int N, bool EN>
+__device__ __forceinline__ void xelast_rows(const XElastArgs& a, const cplx<R>* __restrict__ twg) {
   if (a.skip && *a.skip) return;
   constexpr bool HALF = sizeof(R) == 8;
   using RC = RowCfg<N>;
@@ -597,6 +779,7 @@ __global__ void __launch_bounds__(RowCfg<N>::THREADS, (sizeof(R) == 4 ? 3 : 2))
 #pragma unroll
   for (int f = 0; f < 8; ++f) out[f] = static_cast<cplx<R>*>(a.out[f]) + bs;
 
+  double en = 0.0;
   // Per-thread parking space for one row (each thread reads back only its
   // own values, so no barrier is needed).
   __shared__ cplx<R> stash[RowCfg<N>::THREADS * 8];
@@ -623,6 +806,13 @@ __global__ void __launch_bounds__(RowCfg<N>::THREADS, (sizeof(R) == 4 ? 3 : 2))
         const cplx<R> ax = {ex[j].x * invV, ex[j].y * invV}, by = {ey[j].x * invV, ey[j].y * invV},
                       cz = {ez[j].x * invV, ez[j].y * invV};
         const cplx<R> lt = {l.x * (ax.x + by.x + cz.x), l.y * (ax.y + by.y + cz.y)};
+        if constexpr (EN) {
+          const cplx<R> d2 = {R(2) * (ax.x * ax.x + by.x * by.x + cz.x * cz.x),
+                              R(2) * (ax.y * ax.y + by.y * by.y + cz.y * cz.y)};
+          en += (double)m.x * (double)d2.x + (double)m.y * (double)d2.y + (double)lt.x * (double)(ax.x + by.x + cz.x) +
+                (double)lt.y * (double)(ax.y + by.y + cz.y);
+          pin(en);
+        }
         stash[j * RC::THREADS + threadIdx.x] = {R(2) * m.x * ax.x + lt.x, R(2) * m.y * ax.y + lt.y};
         ey[j] = {R(2) * m.x * by.x + lt.x, R(2) * m.y * by.y + lt.y};
         ez[j] = {R(2) * m.x * cz.x + lt.x, R(2) * m.y * cz.y + lt.y};
@@ -646,7 +836,12 @@ __global__ void __launch_bounds__(RowCfg<N>::THREADS, (sizeof(R) == 4 ? 3 : 2))
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const cplx<R> e = eta[ro + t + TP * j];
-      ux[j] = {e.x * ux[j].x * invV, e.y * ux[j].y * invV};
+      const cplx<R> v = ux[j];
+      ux[j] = {e.x * v.x * invV, e.y * v.y * invV};
+      if constexpr (EN) {
+        en += (double)ux[j].x * (double)(v.x * invV) + (double)ux[j].y * (double)(v.y * invV);
+        pin(en);
+      }
     }
     row_r2c<R, N, HALF>(ux, lds, t, tw);
 #pragma unroll
@@ -665,8 +860,14 @@ __global__ void __launch_bounds__(RowCfg<N>::THREADS, (sizeof(R) == 4 ? 3 : 2))
       const int p = t + TP * j;
       const cplx<R> m = stash[j * RC::THREADS + threadIdx.x];
       const cplx<R> e = eta[ro + p];
-      s[j] = {m.x * s[j].x * invV, m.y * s[j].y * invV};
-      u[j] = {e.x * u[j].x * invV, e.y * u[j].y * invV};
+      const cplx<R> sv = s[j], uv = u[j];
+      s[j] = {m.x * sv.x * invV, m.y * sv.y * invV};
+      u[j] = {e.x * uv.x * invV, e.y * uv.y * invV};
+      if constexpr (EN) {
+        en += (double)s[j].x * (double)(sv.x * invV) + (double)s[j].y * (double)(sv.y * invV) +
+              (double)u[j].x * (double)(uv.x * invV) + (double)u[j].y * (double)(uv.y * invV);
+        pin(en);
+      }
     }
     row_r2c<R, N, HALF>(s, lds, t, tw);
     store_row<R, N>(g == 0 ? out[3] : out[6], s, t, ro);
@@ -682,11 +883,32 @@ __global__ void __launch_bounds__(RowCfg<N>::THREADS, (sizeof(R) == 4 ? 3 : 2))
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const cplx<R> m = stash[j * RC::THREADS + threadIdx.x];
-      s[j] = {m.x * s[j].x * invV, m.y * s[j].y * invV};
+      const cplx<R> sv = s[j];
+      s[j] = {m.x * sv.x * invV, m.y * sv.y * invV};
+      if constexpr (EN) {
+        en += (double)s[j].x * (double)(sv.x * invV) + (double)s[j].y * (double)(sv.y * invV);
+        pin(en);
+      }
     }
     row_r2c<R, N, HALF>(s, lds, t, tw);
     store_row<R, N>(out[5], s, t, ro);
   }
+  if constexpr (EN) {
+    static_assert(RC::THREADS == 64, "one wave per block");
+    en = wave_sum_f(en);
+    if (threadIdx.x == 0) a.epart[row_tile()] = en * ((double)N * N * N);
+  }
+}
+
+template <typename R, int N>
+__global__ void __launch_bounds__(RowCfg<N>::THREADS, (sizeof(R) == 4 ? 3 : 2))
+    k_xelast(XElastArgs a, const cplx<R>* __restrict__ twg) {
+  xelast_rows<R, N, false>(a, twg);
+}
+template <typename R, int N>
+__global__ void __launch_bounds__(RowCfg<N>::THREADS, (sizeof(R) == 4 ? 3 : 2))
+    k_xelast_energy(XElastArgs a, const cplx<R>* __restrict__ twg) {
+  xelast_rows<R, N, true>(a, twg);
 }
 
 // The same pass on small grids: the six outputs-and-their-inputs groups go to
@@ -772,8 +994,9 @@ __global__ void __launch_bounds__(RowCfg<N>::THREADS) k_xelast_layers(XElastArgs
   store_row<R, N>(out(5), s, t, ro);
 }
 
-template <typename R, int N>
-__global__ void __launch_bounds__(RowCfg<N>::THREADS) k_xdiff(XDiffArgs a, const cplx<R>* __restrict__ twg) {
+// EN: also the energy sum of each row tile (XDiffArgs.epart).
+template <typename R, int N, bool EN>
+__device__ __forceinline__ void xdiff_rows(const XDiffArgs& a, const cplx<R>* __restrict__ twg) {
   unsigned act = 0;  // fields to compute (block-uniform)
   for (int f = 0; f < a.ns; ++f)
     if (!(a.skip[f] && *a.skip[f])) act |= 1u << f;
@@ -792,6 +1015,7 @@ __global__ void __launch_bounds__(RowCfg<N>::THREADS) k_xdiff(XDiffArgs a, const
     kr[j] = {k.x * invV, k.y * invV};
   }
   // every row transform of the tile, or on small grids this layer's
+  double en = 0.0;
 #pragma unroll 1
   for (int e = blockIdx.y; e < 3 * a.ns; e += gridDim.y) {
     const int f = e / 3, d = e - 3 * f;
@@ -801,14 +1025,38 @@ __global__ void __launch_bounds__(RowCfg<N>::THREADS) k_xdiff(XDiffArgs a, const
     cplx<R> g[8];
     row_c2r<R, N>(g, static_cast<const cplx<R>*>(a.in[e]) + bs, d == 0, nullptr, lds, t, tw, ro);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) g[j] = {kr[j].x * g[j].x, kr[j].y * g[j].y};
+    for (int j = 0; j < 8; ++j) {
+      const cplx<R> v = g[j];
+      g[j] = {kr[j].x * v.x, kr[j].y * v.y};
+      if constexpr (EN) {
+        en += (double)g[j].x * (double)v.x + (double)g[j].y * (double)v.y;
+        pin(en);
+      }
+    }
     row_r2c<R, N>(g, lds, t, tw);
     if (d == 0) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) g[j] = iwx<R, N>(g[j], t + TP * j);
     }
     store_row<R, N>(static_cast<cplx<R>*>(a.out[e]) + bs, g, t, ro);
+    if constexpr (EN) {
+      static_assert(RC::THREADS == 64, "one wave per block");
+      if (d == 2) {
+        en = wave_sum_f(en);
+        if (threadIdx.x == 0) a.epart[row_tile() * a.ns + f] = en;
+        en = 0.0;
+      }
+    }
   }
+}
+
+template <typename R, int N>
+__global__ void __launch_bounds__(RowCfg<N>::THREADS) k_xdiff(XDiffArgs a, const cplx<R>* __restrict__ twg) {
+  xdiff_rows<R, N, false>(a, twg);
+}
+template <typename R, int N>
+__global__ void __launch_bounds__(RowCfg<N>::THREADS) k_xdiff_energy(XDiffArgs a, const cplx<R>* __restrict__ twg) {
+  xdiff_rows<R, N, true>(a, twg);
 }
 
 template <typename R>
@@ -900,7 +1148,7 @@ __global__ void __launch_bounds__(RowCfg<N>::THREADS) k_xdot(XDotArgs a, const c
 // that overwrites an input would race with the other layers' reads, so such a
 // program keeps one layer.
 inline int col_layers(int n, const ColProg& prog) {
-  if (n > kSplitMaxN || prog.dsv) return 1;
+  if (n > kSplitMaxN) return 1;
   for (int o = 0; o < prog.nout; ++o)
     for (int q = 0; q < prog.nout; ++q)
       for (int k = 0; k < prog.nterm[q]; ++k)
@@ -916,14 +1164,9 @@ void launch_col_pass_seg(int axis, bool inverse, const ColProg& prog, const cplx
   const long long astride = axis == 1 ? C : (long long)NN * C;
   dim3 grid(C / Cfg::TC, NN, col_layers(NN, prog));
   if (inverse)
-    hipLaunchKernelGGL((k_col_pass<R, NN, true, false, SEG>), grid, dim3(Cfg::THREADS), 0, st, prog, fstride,
-                       astride, twp);
-  else if (prog.dsv)
-    hipLaunchKernelGGL((k_col_pass<R, NN, false, true, SEG>), grid, dim3(Cfg::THREADS), 0, st, prog, fstride,
-                       astride, twp);
+    hipLaunchKernelGGL((k_col_pass<R, NN, true, SEG>), grid, dim3(Cfg::THREADS), 0, st, prog, fstride, astride, twp);
   else
-    hipLaunchKernelGGL((k_col_pass<R, NN, false, false, SEG>), grid, dim3(Cfg::THREADS), 0, st, prog, fstride,
-                       astride, twp);
+    hipLaunchKernelGGL((k_col_pass<R, NN, false, SEG>), grid, dim3(Cfg::THREADS), 0, st, prog, fstride, astride, twp);
 }
 
 template <typename R>
@@ -935,39 +1178,47 @@ void launch_col_pass(int n, int axis, bool inverse, const ColProg& prog, const v
   });
 }
 
+// Grids above the small ones (whose Krylov iterations are plane.hpp's).
+#define TUMOR_DISPATCH_LARGE(n, ...)                                                 \
+  switch (n) {                                                                       \
+    case 128: { constexpr int NN = 128; __VA_ARGS__; } break;                        \
+    case 256: { constexpr int NN = 256; __VA_ARGS__; } break;                        \
+    case 512: { constexpr int NN = 512; __VA_ARGS__; } break;                        \
+    default: throw std::runtime_error("no fused passes at " + std::to_string(n));    \
+  }
+
+// (the elasticity's at 256^3 are tile.hpp's)
+[[noreturn]] inline void no_elast_pass() { throw std::logic_error("the elasticity iterates in tile order on this grid"); }
+
 template <typename R>
-int col_pass_blocks(int n, int axis) {
-  int nb = 0;
-  TUMOR_DISPATCH_N(n, {
-    if (col_seg<R>(axis) == 256) nb = (int)((NN / 2) / ColCfg<NN, R, 256>::TC) * NN;
-    else nb = (int)((NN / 2) / ColCfg<NN, R, 128>::TC) * NN;
+void launch_zinv_pupdate(int n, const ZPUpdateArgs& a, const void* tw, hipStream_t st) {
+  const cplx<R>* twp = static_cast<const cplx<R>*>(tw);
+  TUMOR_DISPATCH_LARGE(n, {
+    using Cfg = ZCfg<NN, R>;
+    dim3 grid((NN / 2) / Cfg::TC, NN, a.nsys > 0 ? a.nsys : 1);
+    if (a.nsys > 0) hipLaunchKernelGGL((k_zinv_pupdate_b<R, NN>), grid, dim3(Cfg::THREADS), 0, st, a, twp);
+    else if constexpr (!tile_grid(NN)) hipLaunchKernelGGL((k_zinv_pupdate<R, NN>), grid, dim3(Cfg::THREADS), 0, st, a, twp);
+    else no_elast_pass();
   });
-  return nb;
 }
 
-// (smaller grids' Krylov iterations are plane.hpp's, and the elasticity's at
-// 256^3 tile.hpp's)
 template <typename R>
-void launch_zinv_pupdate(int n, int ncomp, const ZPUpdateArgs& a, const void* tw, hipStream_t st) {
+void launch_zfwd_update(int n, const ZUpdateArgs& a, const void* tw, hipStream_t st) {
   const cplx<R>* twp = static_cast<const cplx<R>*>(tw);
-  auto launch = [&](auto size) {
-    constexpr int NN = decltype(size)::value;
-    using Cfg = ColCfg<NN, R, 256>;
-    dim3 grid((NN / 2) / Cfg::TC, NN);
-    if (a.nsys > 0) {
-      hipLaunchKernelGGL((k_zinv_pupdate_b<R, NN>), dim3(grid.x, grid.y, a.nsys), dim3(Cfg::THREADS), 0, st, a, twp);
-    } else if (ncomp == 1) {
-      hipLaunchKernelGGL((k_zinv_pupdate<R, NN, 1>), grid, dim3(Cfg::THREADS), 0, st, a, twp);
-    } else if constexpr (!tile_grid(NN)) {
-      hipLaunchKernelGGL((k_zinv_pupdate<R, NN, 3>), grid, dim3(Cfg::THREADS), 0, st, a, twp);
-    } else {
-      throw std::logic_error("the elasticity iterates in tile order on this grid");
-    }
-  };
-  if (n == 128) launch(std::integral_constant<int, 128>());
-  else if (n == 256) launch(std::integral_constant<int, 256>());
-  else if (n == 512) launch(std::integral_constant<int, 512>());
-  else throw std::runtime_error("no fused first pass at " + std::to_string(n));
+  TUMOR_DISPATCH_LARGE(n, {
+    using Cfg = ZCfg<NN, R>;
+    dim3 grid((NN / 2) / Cfg::TC, NN, a.nsys > 0 ? a.nsys : 1);
+    if (a.nsys > 0) hipLaunchKernelGGL((k_zfwd_update_b<R, NN>), grid, dim3(Cfg::THREADS), 0, st, a, twp);
+    else if constexpr (!tile_grid(NN)) hipLaunchKernelGGL((k_zfwd_update<R, NN>), grid, dim3(Cfg::THREADS), 0, st, a, twp);
+    else no_elast_pass();
+  });
+}
+
+template <typename R>
+int z_tiles(int n) {
+  int nb = 0;
+  TUMOR_DISPATCH_N(n, nb = (NN / 2) / (ZCfg<NN, R>::TC) * NN);
+  return nb;
 }
 
 template <typename R>
@@ -999,7 +1250,15 @@ void launch_xelast(int n, const XElastArgs& a, const void* tw, hipStream_t st) {
     if constexpr (NN <= kSplitMaxN)
       hipLaunchKernelGGL((k_xelast_layers<R, NN>), dim3(grid.x, 6), dim3(RowCfg<NN>::THREADS), 0, st, a, twp);
     else
+    {
+      if constexpr (!tile_grid(NN)) {
+        if (a.epart) {
+          hipLaunchKernelGGL((k_xelast_energy<R, NN>), grid, dim3(RowCfg<NN>::THREADS), 0, st, a, twp);
+          return;
+        }
+      }
       hipLaunchKernelGGL((k_xelast<R, NN>), grid, dim3(RowCfg<NN>::THREADS), 0, st, a, twp);
+    }
   });
 }
 
@@ -1008,6 +1267,12 @@ void launch_xdiff(int n, const XDiffArgs& a, const void* tw, hipStream_t st) {
   const cplx<R>* twp = static_cast<const cplx<R>*>(tw);
   TUMOR_DISPATCH_N(n, {
     dim3 grid((NN * NN) / RowCfg<NN>::RW, NN <= kSplitMaxN ? 3 * a.ns : 1);
+    if constexpr (!plane_grid(NN)) {
+      if (a.epart) {
+        hipLaunchKernelGGL((k_xdiff_energy<R, NN>), grid, dim3(RowCfg<NN>::THREADS), 0, st, a, twp);
+        return;
+      }
+    }
     hipLaunchKernelGGL((k_xdiff<R, NN>), grid, dim3(RowCfg<NN>::THREADS), 0, st, a, twp);
   });
 }

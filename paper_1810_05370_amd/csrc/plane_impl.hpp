@@ -412,8 +412,8 @@ __device__ __forceinline__ void plane_div(cplx<R> (&g)[8], cplx<R> (&u)[8], cplx
 
 // blockIdx.x: kx plane, blockIdx.y: component; the vector update with the
 // plane in registers.  Bound by five transforms in a chain, the vectors' loads
-// hidden under the last: FP64 32^3 7.4 us, FP32 64^3 14.0, FP64 64^3 21.3 (two
-// waves per SIMD: g, u, w and the vectors are 130 registers and spill a little).
+// hidden under the last: FP32 64^3 14.0 us, FP64 32^3 7.4, 64^3 21.3 (its 256
+// registers leave the scheduler little to hide with).
 template <typename R, int N>
 __global__ void __launch_bounds__((PlaneCfg<R, N>::TH)) k_plane_fwd(PlaneArgs a, const cplx<R>* __restrict__ twg) {
   using T = PlaneCfg<R, N>;

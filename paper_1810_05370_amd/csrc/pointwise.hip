@@ -813,31 +813,6 @@ __global__ void __launch_bounds__(kRedThreads) k_residual(KrylovArgs a, SpecIdx 
   block_store_partials<2>(acc, a.partials);
 }
 
-// Crank-Nicolson start: x0 = c, b = c + h Dc, r = b - (c - h Dc).
-template <typename R>
-__global__ void __launch_bounds__(kRedThreads) k_cn_residual(KrylovArgs a, SpecIdx ix, const cplx<R>* c,
-                                                              const cplx<R>* dc) {
-  const long long S = (long long)a.n * a.n * (a.n / 2);
-  cplx<R>* b = static_cast<cplx<R>*>(a.b);
-  cplx<R>* r = static_cast<cplx<R>*>(a.r);
-  const R h = R(a.pc.h);
-  double acc[2] = {0.0, 0.0};
-  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < S;
-       e += (long long)gridDim.x * blockDim.x) {
-    int kx, ky, kz;
-    ix.decode(e, kx, ky, kz);
-    const cplx<R> cv = c[e], dv = dc[e];
-    const cplx<R> bv = {cv.x + h * dv.x, cv.y + h * dv.y};
-    const cplx<R> av = {cv.x - h * dv.x, cv.y - h * dv.y};
-    const cplx<R> rv = csub(bv, av);
-    b[e] = bv;
-    r[e] = rv;
-    acc[0] += wdot(bv, bv, kx);
-    acc[1] += wdot(rv, rv, kx);
-  }
-  block_store_partials<2>(acc, a.partials);
-}
-
 template <typename R, int NC>
 __global__ void __launch_bounds__(kRedThreads) k_pcg_start(KrylovArgs a, SpecIdx ix, int zero_x) {
   const long long S = (long long)a.n * a.n * (a.n / 2);
@@ -863,84 +838,30 @@ __global__ void __launch_bounds__(kRedThreads) k_pcg_start(KrylovArgs a, SpecIdx
   block_store_partials<1>(acc, a.partials);
 }
 
-// alpha = rho / <p, q>: every block totals the inner-product pass's partials
-// itself, in the order of a one-block totalling kernel, so all blocks agree;
-// block 0 publishes it (or the breakdown) for the deferred x update.
-__device__ __forceinline__ bool pcg_alpha(SolveScalars* sv, const double* part, int nb, int stride, double& alpha) {
-  __syncthreads();  // a previous total in this block has been read (shared buffer)
-  double tot[1];
-  total_partials<1>(tot, part, nb, stride);
-  const bool ok = isfinite(tot[0]) && tot[0] > 0.0;
-  alpha = ok ? sv->rho / tot[0] : 0.0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    sv->pq = tot[0];
-    sv->alpha = alpha;  // 0 on breakdown: nothing left for the deferred x update to add
-    if (!ok) {
-      sv->bad = 1;
-      sv->done = 1;
-    }
-  }
-  return ok;
-}
-
-template <typename R, int NC>
-__global__ void __launch_bounds__(kRedThreads) k_pcg_update(KrylovArgs a, SpecIdx ix) {
-  if (a.sv->done) return;
-  double al;
-  if (!pcg_alpha(a.sv, a.dpart, a.dnb, a.dstride, al)) return;
-  const long long S = (long long)a.n * a.n * (a.n / 2);
-  const R alpha = R(al);
-  cplx<R>* r = static_cast<cplx<R>*>(a.r);
-  const cplx<R>* q = static_cast<const cplx<R>*>(a.q);
-  double acc[2] = {0.0, 0.0};
-  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < S;
-       e += (long long)gridDim.x * blockDim.x) {
-    int kx, ky, kz;
-    ix.decode(e, kx, ky, kz);
-    cplx<R> rv[NC], zv[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const long long k = e + c * S;
-      const cplx<R> qv = q[k];
-      cplx<R> rr = r[k];
-      rr.x -= alpha * qv.x;
-      rr.y -= alpha * qv.y;
-      r[k] = rr;
-      rv[c] = rr;
-    }
-    apply_prec<R, NC>(rv, zv, kx, ky, kz, a.cs, a.pc);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      acc[0] += wdot(rv[c], rv[c], kx);
-      acc[1] += wdot(rv[c], zv[c], kx);
-    }
-  }
-  block_store_partials<2>(acc, a.partials);
-}
-
 // After an update: iteration count, ||r||^2, convergence, beta and rho.
-__global__ void __launch_bounds__(kRedThreads) k_fin_update(KrylovArgs a, int nb) {
-  SolveScalars* sv = a.sv;
-  if (sv->done) return;
-  double tot[2];
-  total_partials<2>(tot, a.partials, nb, kPartialsPerBlock);
-  if (threadIdx.x == 0) {
-    sv->it += 1;
-    sv->rr = tot[0];
-    if (!(isfinite(tot[0]) && isfinite(tot[1]))) {
-      sv->bad = 1;
-      sv->done = 1;
-    } else if (!a.fixed && tot[0] <= a.thr2) {
-      sv->conv = 1;
-      sv->done = 1;
-    } else if (sv->it >= a.limit) {
-      sv->conv = a.fixed ? 1 : 0;
-      sv->done = 1;
-    } else {
-      sv->beta = tot[1] / sv->rho;
-      sv->rho = tot[1];
-    }
+__device__ __forceinline__ void fin_update(SolveScalars* sv, const double (&tot)[2], double thr2, int limit, int fixed) {
+  sv->it += 1;
+  sv->rr = tot[0];
+  if (!(isfinite(tot[0]) && isfinite(tot[1]))) {
+    sv->bad = 1;
+    sv->done = 1;
+  } else if (!fixed && tot[0] <= thr2) {
+    sv->conv = 1;
+    sv->done = 1;
+  } else if (sv->it >= limit) {
+    sv->conv = fixed ? 1 : 0;
+    sv->done = 1;
+  } else {
+    sv->beta = tot[1] / sv->rho;
+    sv->rho = tot[1];
   }
+}
+
+__global__ void __launch_bounds__(kRedThreads) k_fin_update(KrylovArgs a, int nb) {
+  if (a.sv->done) return;
+  double tot[2];
+  total_partials<2>(tot, a.partials, nb, 2);
+  if (threadIdx.x == 0) fin_update(a.sv, tot, a.thr2, a.limit, a.fixed);
 }
 
 // The x update of the last iteration that ran (earlier ones happen in the
@@ -996,15 +917,6 @@ void launch_residual(const KrylovArgs& a, void* r32, hipStream_t st) {
 }
 
 template <typename R>
-void launch_cn_residual(const KrylovArgs& a, const void* c, const void* dc, hipStream_t st) {
-  const SpecIdx ix = make_idx(a.n);
-  const int nb = red_blocks(spec_count(a.n));
-  hipLaunchKernelGGL((k_cn_residual<R>), dim3(nb), dim3(kRedThreads), 0, st, a, ix,
-                     static_cast<const cplx<R>*>(c), static_cast<const cplx<R>*>(dc));
-  hipLaunchKernelGGL(k_fin_resid, dim3(1), dim3(kRedThreads), 0, st, a.sv, a.partials, nb);
-}
-
-template <typename R>
 void launch_pcg_start(const KrylovArgs& a, int zero_x, hipStream_t st) {
   const SpecIdx ix = make_idx(a.n);
   const int nb = red_blocks(spec_count(a.n));
@@ -1013,14 +925,6 @@ void launch_pcg_start(const KrylovArgs& a, int zero_x, hipStream_t st) {
   hipLaunchKernelGGL(k_fin_start, dim3(1), dim3(kRedThreads), 0, st, a.sv, a.partials, nb);
 }
 
-
-template <typename R>
-void launch_pcg_update(const KrylovArgs& a, hipStream_t st) {
-  const SpecIdx ix = make_idx(a.n);
-  const int nb = red_blocks(spec_count(a.n));
-  TUMOR_NC_DISPATCH(a.ncomp, hipLaunchKernelGGL((k_pcg_update<R, NCC>), dim3(nb), dim3(kRedThreads), 0, st, a, ix));
-  hipLaunchKernelGGL(k_fin_update, dim3(1), dim3(kRedThreads), 0, st, a, nb);
-}
 
 void launch_fin_update(const KrylovArgs& a, int nb, hipStream_t st) {
   hipLaunchKernelGGL(k_fin_update, dim3(1), dim3(kRedThreads), 0, st, a, nb);
@@ -1294,75 +1198,15 @@ __global__ void __launch_bounds__(kRedThreads) k_bfin_start(SolveScalars* sv, in
   }
 }
 
-template <typename R>
-__global__ void __launch_bounds__(kRedThreads) k_bpcg_update(BatchArgs a, SpecIdx ix) {
-  const long long S = (long long)a.n * a.n * (a.n / 2);
-  cplx<R>* r = static_cast<cplx<R>*>(a.r);
-  const cplx<R>* q = static_cast<const cplx<R>*>(a.q);
-  bool run[kMaxSys];
-  R alpha[kMaxSys];
-  bool any = false;
-#pragma unroll
-  for (int s = 0; s < kMaxSys; ++s) {
-    run[s] = s < a.ns && !a.sv[s].done;  // block-uniform
-    double al = 0.0;
-    if (run[s]) run[s] = pcg_alpha(a.sv + s, a.dpart + s, a.dnb, kDotStride, al);
-    alpha[s] = R(al);
-    any = any || run[s];
-  }
-  if (!any) return;
-  double acc[2 * kMaxSys] = {};
-  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < S;
-       e += (long long)gridDim.x * blockDim.x) {
-    int kx, ky, kz;
-    ix.decode(e, kx, ky, kz);
-#pragma unroll
-    for (int s = 0; s < kMaxSys; ++s) {
-      if (!run[s]) continue;
-      const long long k = e + s * S;
-      const cplx<R> qv = q[k];
-      cplx<R> rr = r[k];
-      rr.x -= alpha[s] * qv.x;
-      rr.y -= alpha[s] * qv.y;
-      r[k] = rr;
-      cplx<R> rv[1] = {rr}, zv[1];
-      apply_prec<R, 1>(rv, zv, kx, ky, kz, a.cs, a.pc);
-      acc[s] += wdot(rv[0], rv[0], kx);
-      acc[kMaxSys + s] += wdot(rv[0], zv[0], kx);
-    }
-  }
-  block_store_partials<2 * kMaxSys>(acc, a.partials);
-}
-
-// Per system not done: iteration count, ||r||^2, convergence, beta and rho.
+// After an update, per system (a block each): iteration count, ||r||^2,
+// convergence, beta and rho.
 __global__ void __launch_bounds__(kRedThreads) k_bfin_update(BatchArgs a, int nb) {
-  bool any = false;
-  for (int s = 0; s < a.ns; ++s) any = any || !a.sv[s].done;
-  if (!any) return;
-  double tot[2 * kMaxSys];
-  total_partials<2 * kMaxSys>(tot, a.partials, nb, kPartialsPerBlock);
-  if (threadIdx.x == 0) {
-    for (int s = 0; s < a.ns; ++s) {
-      SolveScalars* sv = a.sv + s;
-      if (sv->done) continue;
-      const double rr = tot[s], rz = tot[kMaxSys + s];
-      sv->it += 1;
-      sv->rr = rr;
-      if (!(isfinite(rr) && isfinite(rz))) {
-        sv->bad = 1;
-        sv->done = 1;
-      } else if (!a.fixed[s] && rr <= a.thr2[s]) {
-        sv->conv = 1;
-        sv->done = 1;
-      } else if (sv->it >= a.limit[s]) {
-        sv->conv = a.fixed[s] ? 1 : 0;
-        sv->done = 1;
-      } else {
-        sv->beta = rz / sv->rho;
-        sv->rho = rz;
-      }
-    }
-  }
+  const int s = blockIdx.x;
+  SolveScalars* sv = a.sv + s;
+  if (sv->done) return;
+  double tot[2];
+  total_partials<2>(tot, a.partials + 2LL * nb * s, nb, 2);
+  if (threadIdx.x == 0) fin_update(sv, tot, a.thr2[s], a.limit[s], a.fixed[s]);
 }
 
 // x_k += alpha_k p_k for the last iteration each system ran (none: no-op).
@@ -1423,13 +1267,8 @@ void launch_bpcg_start(const BatchArgs& a, int zero_x, hipStream_t st) {
   hipLaunchKernelGGL(k_bfin_start, dim3(1), dim3(kRedThreads), 0, st, a.sv, a.ns, a.active, a.partials, nb);
 }
 
-
-template <typename R>
-void launch_bpcg_update(const BatchArgs& a, hipStream_t st) {
-  const SpecIdx ix = make_idx(a.n);
-  const int nb = red_blocks(spec_count(a.n));
-  hipLaunchKernelGGL((k_bpcg_update<R>), dim3(nb), dim3(kRedThreads), 0, st, a, ix);
-  hipLaunchKernelGGL(k_bfin_update, dim3(1), dim3(kRedThreads), 0, st, a, nb);
+void launch_bfin_update(const BatchArgs& a, int nb, hipStream_t st) {
+  hipLaunchKernelGGL(k_bfin_update, dim3(a.ns), dim3(kRedThreads), 0, st, a, nb);
 }
 
 template <typename R>
@@ -1452,15 +1291,12 @@ void launch_badd32to64(void* x64, const void* x32, const double (&s)[kMaxSys], i
 
 #define TUMOR_INST_KRYLOV(R)                                                               \
   template void launch_residual<R>(const KrylovArgs&, void*, hipStream_t);                 \
-  template void launch_cn_residual<R>(const KrylovArgs&, const void*, const void*, hipStream_t); \
   template void launch_pcg_start<R>(const KrylovArgs&, int, hipStream_t);                  \
-  template void launch_pcg_update<R>(const KrylovArgs&, hipStream_t);                      \
   template void launch_pcg_xfinal<R>(const KrylovArgs&, hipStream_t);                      \
   template void launch_precond<R>(const KrylovArgs&, const void*, void*, hipStream_t);     \
   template void launch_bresidual<R>(const BatchArgs&, void*, hipStream_t);                 \
   template void launch_bcn_residual<R>(const BatchArgs&, const void*, const void*, hipStream_t); \
   template void launch_bpcg_start<R>(const BatchArgs&, int, hipStream_t);                  \
-  template void launch_bpcg_update<R>(const BatchArgs&, hipStream_t);                      \
   template void launch_bpcg_xfinal<R>(const BatchArgs&, hipStream_t);
 TUMOR_INST_KRYLOV(double)
 TUMOR_INST_KRYLOV(float)

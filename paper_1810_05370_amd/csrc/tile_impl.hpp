@@ -52,15 +52,6 @@ __device__ __forceinline__ cplx<R> r2c_mix(cplx<R> A, cplx<R> B, cplx<R> w, bool
   return {zero ? A.x + A.y : R(0.5) * (s.x + wd.y), zero ? A.x - A.y : R(0.5) * (s.y - wd.x)};
 }
 
-// Has v computed by this point (and its operands' registers free).
-__device__ __forceinline__ void pin(double& v) { asm volatile("" : "+v"(v)); }
-
-// The same value, not known to be computable before this point.
-__device__ __forceinline__ int opaque(int v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
 // Transform of a line of 16 B points held by B threads: v[j] is position
 // t + B j on entry and on return.  buf(m, t): exchange cell.  WAVE: the line's
 // threads are lanes of one wave.  TWS: table entries per w_(16 B).
@@ -253,48 +244,6 @@ __global__ void __launch_bounds__((TileCfg<R, N>::TA), (sizeof(R) == 4 ? 4 : 2))
   z_store(v, 7);
 }
 
-// Totals of a block of TH threads (fixed order), valid in every thread; sh:
-// NV * TH / 64 doubles of LDS that nothing else is using.
-template <int NV, int TH>
-__device__ __forceinline__ void block_totals(double (&v)[NV], double* sh) {
-  constexpr int NW = TH / 64;
-  static_assert(TH % 64 == 0, "whole waves");
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const double s = wave_sum_f(v[i]);
-    if (lane == 0) sh[i * NW + wv] = s;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    double s = 0.0;
-    for (int k = 0; k < NW; ++k) s += sh[i * NW + k];
-    v[i] = s;
-  }
-}
-
-// alpha = rho / <p, A p> from the x side's nb parts (every block totals them
-// in the same order); block 0 publishes it, or the breakdown.
-template <int TH>
-__device__ __forceinline__ bool tile_alpha(SolveScalars* sv, const double* part, int nb, double* sh, double& alpha) {
-  double tot[1] = {0.0};
-  for (int k = threadIdx.x; k < nb; k += TH) tot[0] += part[k];
-  block_totals<1, TH>(tot, sh);
-  const bool ok = isfinite(tot[0]) && tot[0] > 0.0;
-  alpha = ok ? sv->rho / tot[0] : 0.0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    sv->pq = tot[0];
-    sv->alpha = alpha;
-    if (!ok) {
-      sv->bad = 1;
-      sv->done = 1;
-    }
-  }
-  return ok;
-}
-
 template <typename R, int N>
 __global__ void __launch_bounds__((TileCfg<R, N>::TA), (sizeof(R) == 4 ? 4 : 2)) k_tile_fwd(TileFwdArgs a, const cplx<R>* __restrict__ twg) {
   using T = TileCfg<R, N>;
@@ -308,7 +257,7 @@ __global__ void __launch_bounds__((TileCfg<R, N>::TA), (sizeof(R) == 4 ? 4 : 2))
   const long long tbase = (long long)tile * 16 * T::TA;
   auto at = [&](void* vec, int c, int e) { return static_cast<cplx<R>*>(vec) + (tbase + c * S + e * T::TA); };
   double al;
-  if (!tile_alpha<T::TA>(a.sv, a.epart, T::NB, reinterpret_cast<double*>(buf), al)) return;
+  if (!block_alpha<T::TA>(a.sv, a.epart, T::NB, blockIdx.x == 0, reinterpret_cast<double*>(buf), al)) return;
   const R alpha = R(al);
   for (int k = tid; k < N; k += T::TA) stw[k] = twg[k];
   const int kz = wavenum<N>(th.iz);
@@ -387,8 +336,8 @@ __global__ void __launch_bounds__((TileCfg<R, N>::TA), (sizeof(R) == 4 ? 4 : 2))
   acc[1] *= wt;
   block_totals<2, T::TA>(acc, reinterpret_cast<double*>(buf));
   if (threadIdx.x == 0) {
-    a.partials[(long long)blockIdx.x * kPartialsPerBlock] = acc[0];
-    a.partials[(long long)blockIdx.x * kPartialsPerBlock + 1] = acc[1];
+    a.partials[2 * (long long)blockIdx.x] = acc[0];
+    a.partials[2 * (long long)blockIdx.x + 1] = acc[1];
   }
 }
 

@@ -1,5 +1,5 @@
-"""The elasticity solve on every grid size its kernels are written for, against
-the oracle: in iteration lockstep in FP64 (a few iterations, where every
+"""The solves on every grid size their kernels are written for, against the
+oracle: in iteration lockstep in FP64 (a few iterations, where every
 operator, inner product and update counts), and by the FP64 residual of its
 result in the mixed precision.
 
@@ -17,6 +17,7 @@ import pytest
 import paper_1810_05370_amd as tm
 import synthetic
 from gpu_common import need_gpu, rel_l2, say
+from oracle import model, model_single
 from oracle import reaction as rx
 from oracle import solvers
 from oracle.spectral import Grid, norm
@@ -76,3 +77,26 @@ def test_mixed_elasticity_meets_its_tolerance(n):
     say(f"  {it} iterations, residual {rr:.3e}, by the oracle {rel:.3e}")
     sim.close()
     assert it > 0 and rel <= 1.01e-8 and abs(rel - rr) <= 1e-10
+
+
+@pytest.mark.parametrize("n", [16, 128, 256])
+def test_diffusion_in_lockstep(n):
+    """One species, so the solve is a batch of one: diffusion and reaction, three iterations."""
+    need_gpu()
+    say(f"diffusion lockstep n={n}")
+    inp = synthetic.workload_inputs("seeds3_n128", n=n)
+    P = synthetic.params()
+    st = model.init_state(P, n, inp["wm"], inp["gm"], inp["csf"], inp["centers"], inp["sigmas"], inp["weights"])
+    ref = model_single.step(st, dict(advection=False, elasticity=False), forced=[3, 0, 0, 0])
+    sim = tm.from_inputs(inp, P, model="single", flags=0)
+    sim.force_iterations([3, 0, 0, 0])
+    got = sim.step(1)
+    err = rel_l2(sim.get("p").cpu().numpy(), st.f["p"])
+    rr, rr_ref = got["relres_diff"][0], ref["relres_diff"][0]
+    say(f"  relL2 {err:.2e}, residual {rr:.3e} (oracle {rr_ref:.3e})")
+    sim.close()
+    assert got["it_diff"][0] == 3
+    assert err < 1e-11
+    # the residual after three iterations is a difference of terms about 1 / rr_ref
+    # times its size, each rounded to 1e-16
+    assert abs(rr - rr_ref) <= 1e-9 * rr_ref + 1e-13
