@@ -404,13 +404,14 @@ __device__ __forceinline__ void tile_taps(const double* tile, const StencilD& s,
 // Stage the box of G fields into the tile (between barriers: the previous
 // readers of the tile are done, and every thread sees the new contents).
 template <int G>
-__device__ __forceinline__ void tile_load(double* tile, const double* const (&src)[G], const int (&box)[3],
-                                          const int (&L)[3], int n) {
-  double sc[G];
+__device__ __forceinline__ void tile_load(double* tile, const double* const (&src)[G],
+                                          const BoxNodes<kSlAdjTile / 256>& nodes) {
+  double v[kSlAdjTile / 256][G], sc[G];
 #pragma unroll
   for (int g = 0; g < G; ++g) sc[g] = 1.0;
+  nodes.load<G>(v, src);
   __syncthreads();
-  tile_stage<double, G>(tile, src, sc, box[0], box[1], box[2], L, n);
+  nodes.put<double, G>(tile, v, sc);
   __syncthreads();
 }
 
@@ -592,7 +593,7 @@ __global__ void __launch_bounds__(256) k_sl_adj_finish(SLAdjArgs a, const GradSc
 // recomputed from the departure points where they are needed, rather than
 // held across the gathers and scatters, so that the kernel stays within the
 // register file.
-__global__ void __launch_bounds__(kSlAdjThreads) k_sl_adj(SLAdjArgs a, const GradScalars* gs) {
+__global__ void __launch_bounds__(kSlAdjThreads, 3) k_sl_adj(SLAdjArgs a, const GradScalars* gs) {
   __shared__ __align__(16) long long tile[2 * kSlAdjTile];
   __shared__ double sval[10][kSlAdjThreads];
   __shared__ double* sout[10];
@@ -624,8 +625,10 @@ __global__ void __launch_bounds__(kSlAdjThreads) k_sl_adj(SLAdjArgs a, const Gra
     block_box(lo, hi, red);
     fits1 = box_fits(lo, hi, n, kSlAdjTile, box1, L1);
     if (fits1) {
+      BoxNodes<kSlAdjTile / 256> nodes;
+      nodes.set(box1, L1, n);
       const double* const s01[2] = {a.vx, a.vy};
-      tile_load<2>(dtile, s01, box1, L1, n);
+      tile_load<2>(dtile, s01, nodes);
       tile_taps<2>(dtile, st, box1, L1, [&](const double (&q)[2], double w, double wgx, double wgy, double wgz) {
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
@@ -636,7 +639,7 @@ __global__ void __launch_bounds__(kSlAdjThreads) k_sl_adj(SLAdjArgs a, const Gra
         }
       });
       const double* const s2[1] = {a.vz};
-      tile_load<1>(dtile, s2, box1, L1, n);
+      tile_load<1>(dtile, s2, nodes);
       tile_taps<1>(dtile, st, box1, L1, [&](const double (&q)[1], double w, double wgx, double wgy, double wgz) {
         vs[2] += w * q[0];
         gv[2][0] += wgx * q[0];
@@ -660,6 +663,8 @@ __global__ void __launch_bounds__(kSlAdjThreads) k_sl_adj(SLAdjArgs a, const Gra
     block_box(lo, hi, red);
     fits2 = box_fits(lo, hi, n, kSlAdjTile, box2, L2);
     if (fits2) {
+      BoxNodes<kSlAdjTile / 256> nodes;
+      nodes.set(box2, L2, n);
 #pragma unroll
       for (int k = 0; k < 4; ++k) e[k] = dq[k] = 0.0;
       e5[0] = e5[1] = e5[2] = 0.0;
@@ -670,17 +675,17 @@ __global__ void __launch_bounds__(kSlAdjThreads) k_sl_adj(SLAdjArgs a, const Gra
         e[3] += wgz * c;
       };
       const double* const p01[2] = {a.q[0], a.q[1]};
-      tile_load<2>(dtile, p01, box2, L2, n);
+      tile_load<2>(dtile, p01, nodes);
       tile_taps<2>(dtile, st, box2, L2, [&](const double (&q)[2], double w, double wgx, double wgy, double wgz) {
         acc_e(lam[0] * q[0] + lam[1] * q[1], w, wgx, wgy, wgz);
       });
       const double* const p23[2] = {a.q[2], a.q[3]};
-      tile_load<2>(dtile, p23, box2, L2, n);
+      tile_load<2>(dtile, p23, nodes);
       tile_taps<2>(dtile, st, box2, L2, [&](const double (&q)[2], double w, double wgx, double wgy, double wgz) {
         acc_e(lam[2] * q[0] + lam[3] * q[1], w, wgx, wgy, wgz);
       });
       const double* const p45[2] = {a.q[4], a.q[5]};
-      tile_load<2>(dtile, p45, box2, L2, n);
+      tile_load<2>(dtile, p45, nodes);
       tile_taps<2>(dtile, st, box2, L2, [&](const double (&q)[2], double w, double wgx, double wgy, double wgz) {
         acc_e(lam[4] * q[0], w, wgx, wgy, wgz);
         const double c5 = lam[5] * q[1];
@@ -689,7 +694,7 @@ __global__ void __launch_bounds__(kSlAdjThreads) k_sl_adj(SLAdjArgs a, const Gra
         e5[2] += wgz * c5;
       });
       const double* const pd[1] = {a.div};
-      tile_load<1>(dtile, pd, box2, L2, n);
+      tile_load<1>(dtile, pd, nodes);
       tile_taps<1>(dtile, st, box2, L2, [&](const double (&q)[1], double w, double wgx, double wgy, double wgz) {
         dq[0] += w * q[0];
         dq[1] += wgx * q[0];

@@ -512,6 +512,14 @@ __device__ __forceinline__ void block_max_cfl(double c, CoefScalars* cs) {
 // Departure points and the stencil weights' arguments stay FP64.  Within a
 // voxel the tap order (z, then y, then x; weight wz wy, then times wx) is
 // fixed, so every path gives the same bits.
+//
+// Bound by LDS reads in FP64 (80 bytes per tap and voxel, about 75 % of the
+// kernel's time) and by the passes' round trips in FP32; a tile pitch that is a
+// multiple of 8 or 16 nodes more than doubles the bank conflicts (FP64 2.42 and
+// 2.72 ms).  At 256^3 1.88 ms in FP64, 2.1 in FP32; with a loop over the nodes to
+// stage a box and the fallback's 64 taps unrolled (199 registers, 2 waves per
+// SIMD) 2.24 and 2.15.  Loading the next pass's box during a gather spills (FP64
+// 4.5 ms); FP32 at 4 waves per SIMD is slower (2.2).
 
 // Stencil of one point: base node floor(X) - 1 per axis and the weights.
 template <typename RC>
@@ -557,13 +565,18 @@ template <typename RC, int G>
 __device__ __forceinline__ void global_gather(const double* const (&src)[G], const double (&sc)[G],
                                               const Stencil<RC>& st, int n, RC* out) {
   const int m = n - 1;
-#pragma unroll
+  // rows one at a time: unrolled, the compiler loads all 64 taps ahead, and the
+  // registers for that cost the kernel a wave per SIMD
+  const RC z0 = st.wz[0], z1 = st.wz[1], z2 = st.wz[2], z3 = st.wz[3];
+  const RC y0 = st.wy[0], y1 = st.wy[1], y2 = st.wy[2], y3 = st.wy[3];
+#pragma unroll 1
   for (int c = 0; c < 4; ++c) {
     const long long zo = (long long)((st.iz + c - 1) & m) * n * n;
-#pragma unroll
+#pragma unroll 1
     for (int b = 0; b < 4; ++b) {
       const long long yo = zo + (long long)((st.iy + b - 1) & m) * n;
-      const RC wzy = st.wz[c] * st.wy[b];
+      const RC wz = c < 2 ? (c == 0 ? z0 : z1) : (c == 2 ? z2 : z3);
+      const RC wzy = wz * (b < 2 ? (b == 0 ? y0 : y1) : (b == 2 ? y2 : y3));
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         const long long idx = yo + ((st.ix + a - 1) & m);
@@ -576,29 +589,45 @@ __device__ __forceinline__ void global_gather(const double* const (&src)[G], con
   }
 }
 
-// One gather pass of G fields for all voxels of the thread.
-template <typename RC, int G, int VPT>
-__device__ __forceinline__ void sl_pass(RC* tile, bool fits, const double* const (&src)[G], const double (&sc)[G],
-                                        const int (&box)[3], const int (&L)[3], const Stencil<RC> (&st)[VPT],
-                                        int n, RC (&acc)[VPT][8], int slot) {
-  if (fits) {
-    __syncthreads();  // the previous pass has finished reading the tile
-    tile_stage<RC, G>(tile, src, sc, box[0], box[1], box[2], L, n);
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < VPT; ++k) tile_gather<RC, G>(tile, st[k], box[0], box[1], box[2], L, &acc[k][slot]);
-  } else {
-#pragma unroll
-    for (int k = 0; k < VPT; ++k) global_gather<RC, G>(src, sc, st[k], n, &acc[k][slot]);
+// The gather passes of a stage.
+template <typename RC, int VPT, int SLOTS>
+struct SlStage {
+  RC* tile;
+  bool fits;
+  const int (&box)[3];
+  const int (&L)[3];
+  const Stencil<RC> (&st)[VPT];
+  int n;
+  RC (&acc)[VPT][8];
+  BoxNodes<SLOTS> nodes;
+
+  __device__ __forceinline__ void begin() {
+    if (fits) nodes.set(box, L, n);
   }
-}
+  template <int G>
+  __device__ __forceinline__ void pass(const double* const (&src)[G], const double (&sc)[G], int slot) const {
+    if (fits) {
+      double v[SLOTS][G];
+      nodes.template load<G>(v, src);
+      __syncthreads();  // the previous pass has finished reading the tile
+      nodes.template put<RC, G>(tile, v, sc);
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < VPT; ++k) tile_gather<RC, G>(tile, st[k], box[0], box[1], box[2], L, &acc[k][slot]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < VPT; ++k) global_gather<RC, G>(src, sc, st[k], n, &acc[k][slot]);
+    }
+  }
+};
 
 template <typename RC, int BX, int BY, int BZ, int CAP>
-__global__ void __launch_bounds__(256) k_sl_tile(SLArgs a, CoefScalars* cs) {
+__global__ void __launch_bounds__(256, 3) k_sl_tile(SLArgs a, CoefScalars* cs) {
   constexpr int ZS = 256 / (BX * BY);        // z distance of a thread's voxels
   constexpr int VPT = BZ / ZS;
   static_assert(256 % (BX * BY) == 0 && BZ % ZS == 0, "brick shape");
   constexpr int GV = sizeof(RC) == 4 ? 4 : 2;  // values per 16-byte LDS node
+  constexpr int SLOTS = CAP / 256;
   __shared__ __align__(16) RC tile[CAP * (16 / sizeof(RC))];   // CAP 16-byte nodes
   __shared__ int red[24];
   const int n = a.n_grid;
@@ -650,17 +679,17 @@ __global__ void __launch_bounds__(256) k_sl_tile(SLArgs a, CoefScalars* cs) {
   for (int k = 0; k < VPT; ++k)
 #pragma unroll
     for (int g = 0; g < 8; ++g) acc[k][g] = RC(0);
-  const double one[4] = {1.0, 1.0, 1.0, 1.0};
-  const double one1[1] = {1.0};
+  const double one[4] = {1.0, 1.0, 1.0, 1.0}, one2[2] = {1.0, 1.0}, one1[1] = {1.0};
+  SlStage<RC, VPT, SLOTS> sg{tile, fits, box, L, st, n, acc, {}};
+  sg.begin();
   if constexpr (GV == 4) {
     const double* const src[4] = {a.vx, a.vy, a.vz, nullptr};
-    sl_pass<RC, 4, VPT>(tile, fits, src, one, box, L, st, n, acc, 0);
+    sg.pass(src, one, 0);
   } else {
     const double* const s2[2] = {a.vx, a.vy};
     const double* const s1[1] = {a.vz};
-    const double one2[2] = {1.0, 1.0};
-    sl_pass<RC, 2, VPT>(tile, fits, s2, one2, box, L, st, n, acc, 0);
-    sl_pass<RC, 1, VPT>(tile, fits, s1, one1, box, L, st, n, acc, 2);
+    sg.pass(s2, one2, 0);
+    sg.pass(s1, one1, 2);
   }
   // stage 2: departure points X, then the seven fields there
   lo[0] = lo[1] = lo[2] = INT_MAX;
@@ -686,23 +715,25 @@ __global__ void __launch_bounds__(256) k_sl_tile(SLArgs a, CoefScalars* cs) {
   double sc[6];
 #pragma unroll
   for (int f = 0; f < 6; ++f) sc[f] = sizeof(RC) == sizeof(double) ? 1.0 : pow2_scale(cs->qmax_bits[f]);
+  sg.fits = fits;
+  sg.begin();
   if constexpr (GV == 4) {
     const double* const q0[4] = {a.p, a.i, a.n, a.g};
     const double* const q1[4] = {a.w, a.f, a.div, nullptr};
     const double s0[4] = {sc[0], sc[1], sc[2], sc[3]};
     const double s1[4] = {sc[4], sc[5], 1.0, 1.0};
-    sl_pass<RC, 4, VPT>(tile, fits, q0, s0, box, L, st, n, acc, 0);
-    sl_pass<RC, 4, VPT>(tile, fits, q1, s1, box, L, st, n, acc, 4);
+    sg.pass(q0, s0, 0);
+    sg.pass(q1, s1, 4);
   } else {
     const double* const q0[2] = {a.p, a.i};
     const double* const q1[2] = {a.n, a.g};
     const double* const q2[2] = {a.w, a.f};
     const double* const q3[1] = {a.div};
     const double s0[2] = {sc[0], sc[1]}, s1[2] = {sc[2], sc[3]}, s2[2] = {sc[4], sc[5]};
-    sl_pass<RC, 2, VPT>(tile, fits, q0, s0, box, L, st, n, acc, 0);
-    sl_pass<RC, 2, VPT>(tile, fits, q1, s1, box, L, st, n, acc, 2);
-    sl_pass<RC, 2, VPT>(tile, fits, q2, s2, box, L, st, n, acc, 4);
-    sl_pass<RC, 1, VPT>(tile, fits, q3, one1, box, L, st, n, acc, 6);
+    sg.pass(q0, s0, 0);
+    sg.pass(q1, s1, 2);
+    sg.pass(q2, s2, 4);
+    sg.pass(q3, one1, 6);
   }
   const RC dt = RC(a.dt);
   double* const outs[6] = {a.po, a.io, a.no, a.go, a.wo, a.fo};

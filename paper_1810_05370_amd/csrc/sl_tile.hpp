@@ -4,7 +4,7 @@
 // reduces the floors of its departure points to their bounding box
 // (block_box), widens it by the tricubic stencil's reach -1 .. +2
 // (box_fits), copies that box of the needed fields from HBM into LDS once
-// (tile_stage: coalesced rows, periodic wrap), and its voxels then read their
+// (BoxNodes: coalesced rows, periodic wrap), and its voxels then read their
 // 64 taps from the tile.  Nodes hold G values of one type (a 16-byte node:
 // 4 FP32 or 2 FP64 values; 8 bytes for a single FP64 value).
 #pragma once
@@ -73,26 +73,67 @@ __device__ __forceinline__ void block_box(int (&lo)[3], int (&hi)[3], int* sh /*
   __syncthreads();  // sh is reused by the next reduction
 }
 
-// Copy the box [x0, x0+L[0]) x [y0, ...) x [z0, ...) (unwrapped) of G fields
-// into the tile, node (xr, yr, zr) at ((zr L[1] + yr) L[0] + xr).  A null
-// source fills its slot with zeros (padding of a 16-byte node).
-template <typename RC, int G>
-__device__ __forceinline__ void tile_stage(RC* tile, const double* const (&src)[G], const double (&sc)[G], int x0,
-                                           int y0, int z0, const int (&L)[3], int n) {
-  const int m = n - 1;
-  const int rows = L[1] * L[2];
-  for (int e = threadIdx.x; e < rows * L[0]; e += 256) {
-    const int row = e / L[0];
-    const int xr = e - row * L[0];
-    const int zr = row / L[1];
-    const int yr = row - zr * L[1];
-    const long long gi = ((long long)((z0 + zr) & m) * n + ((y0 + yr) & m)) * n + ((x0 + xr) & m);
-    RC v[G];
+// The nodes t, t + 256, ... (at most SLOTS) of the box [box, box + L) (unwrapped)
+// as offsets into the fields, worked out once for all passes of a stage; node
+// (xr, yr, zr) lies at ((zr L[1] + yr) L[0] + xr) of the tile.  A pass is one
+// batch of loads (load) and one of LDS stores (put): a single round trip to
+// memory, where a loop over the nodes took one per 256 nodes, and no division.
+template <int SLOTS>
+struct BoxNodes {
+  unsigned off[SLOTS];
+  int nodes;
+
+  __device__ __forceinline__ void set(const int (&box)[3], const int (&Lv)[3], int n) {
+    const int m = n - 1;
+    const int L0 = __builtin_amdgcn_readfirstlane(Lv[0]), L1 = __builtin_amdgcn_readfirstlane(Lv[1]);
+    nodes = L0 * L1 * __builtin_amdgcn_readfirstlane(Lv[2]);
+    // 256 nodes on: dx + L0 (dy + L1 dz)
+    const int q = 256 / L0, dx = 256 - q * L0, dz = q / L1, dy = q - dz * L1;
+    const int row = (int)threadIdx.x / L0;
+    int xr = (int)threadIdx.x - row * L0;
+    int zr = row / L1, yr = row - zr * L1;
 #pragma unroll
-    for (int g = 0; g < G; ++g) v[g] = src[g] ? RC(sc[g] * src[g][gi]) : RC(0);
-    tile_put<G, RC>(tile, e, v);
+    for (int k = 0; k < SLOTS; ++k) {
+      // (wrapped, so beyond the last node too an element of the fields)
+      off[k] = ((unsigned)((box[2] + zr) & m) * (unsigned)n + (unsigned)((box[1] + yr) & m)) * (unsigned)n +
+               (unsigned)((box[0] + xr) & m);
+      xr += dx;
+      yr += dy;
+      zr += dz;
+      if (xr >= L0) {
+        xr -= L0;
+        ++yr;
+      }
+      if (yr >= L1) {
+        yr -= L1;
+        ++zr;
+      }
+    }
   }
-}
+  // a null source fills its value with zeros (padding of a 16-byte node)
+  template <int G>
+  __device__ __forceinline__ void load(double (&v)[SLOTS][G], const double* const (&src)[G]) const {
+#pragma unroll
+    for (int k = 0; k < SLOTS; ++k)
+      if (k * 256 < nodes) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) v[k][g] = src[g] ? src[g][off[k]] : 0.0;
+      }
+  }
+  template <typename RC, int G>
+  __device__ __forceinline__ void put(RC* tile, const double (&v)[SLOTS][G], const double (&sc)[G]) const {
+#pragma unroll
+    for (int k = 0; k < SLOTS; ++k) {
+      const int e = (int)threadIdx.x + k * 256;
+      if (e < nodes) {
+        RC t[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) t[g] = RC(sc[g] * v[k][g]);
+        tile_put<G, RC>(tile, e, t);
+      }
+    }
+  }
+};
 
 // Box of the stencils whose floors span [lo, hi] per axis: origin lo - 1,
 // extent hi - lo + 4.  It fits when it is no wider than the grid plus the
