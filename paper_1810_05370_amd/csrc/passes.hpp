@@ -213,7 +213,7 @@ template <typename R>
 void launch_xdot(int n, const XDotArgs& a, const void* tw, hipStream_t st);
 template <typename R>
 void launch_zfwd_update(int n, const ZUpdateArgs& a, const void* tw, hipStream_t st);
-// tiles of a fused first or last pass (the count of its partials)
+// tiles of a fused last pass (the count of its partials)
 template <typename R>
 int z_tiles(int n);
 // row tiles of an x pass (RowCfg: one wave of 64 threads, n / 16 to a row)

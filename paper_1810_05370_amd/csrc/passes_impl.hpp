@@ -28,19 +28,21 @@ __device__ __forceinline__ int opaque(int v) {
 // along the transformed axis.  Measured at 256^3: z passes, whose positions
 // lie a whole plane apart, run faster with 256-byte segments; FP32 y passes
 // with 128-byte segments (and twice the blocks).
-template <int N, typename R, int SEG = 128>
+template <int N, typename R, int SEG = 128, int MT = (sizeof(R) == 8 ? 512 : 1024)>
 struct ColCfg {
   static constexpr int TP = N / 8;
   static constexpr int TCW = 256 / TP;
   static constexpr int TCMIN = SEG / (2 * (int)sizeof(R));
   static constexpr int TC00 = TCW < TCMIN ? TCMIN : TCW;
-  // at most 1024 threads per block, 512 in FP64 (whose passes need more
-  // than the 128 VGPRs a 16-wave block leaves)
-  static constexpr int MAXT = sizeof(R) == 8 ? 512 : 1024;
+  // at most MT threads per block: by default 1024, 512 in FP64 (whose passes
+  // need more than the 128 VGPRs a 16-wave block leaves)
+  static constexpr int MAXT = MT;
   static constexpr int TC0 = TC00 * TP > MAXT ? MAXT / TP : TC00;
   static constexpr int TC = (N / 2) < TC0 ? (N / 2) : TC0;
   static constexpr int THREADS = TC * TP;
   static constexpr int LDS = N * TC + N / 8 + 1;
+  // FP64 in 1024 threads: 128 registers, no room for whole vectors
+  static constexpr bool LEAN = sizeof(R) == 8 && THREADS == 1024;
 };
 
 // Segment width of a column pass: 256 bytes for z passes and for FP64.
@@ -50,6 +52,13 @@ constexpr int col_seg(int axis) { return (axis == 2 || sizeof(R) == 8) ? 256 : 1
 // Tiles of the fused first and last passes of a Krylov apply.
 template <int N, typename R>
 using ZCfg = ColCfg<N, R, 256>;
+// The elasticity's first pass: FP64 at 512^3 in blocks of 1024 threads, for
+// segments of 256 bytes.  Its 21 arrays are read and written 2 MB apart, and
+// there the segment counts for more than registers: 5.98 ms, against 6.86 with
+// 512 threads and 128 bytes (p held in registers), 7.38 with two such blocks to
+// a CU (p read back).  The last pass spills in 128 registers (4.24 for 4.02 ms).
+template <int N, typename R>
+using ZWideCfg = ColCfg<N, R, 256, 1024>;
 
 // Copy the twiddle table into LDS (all threads), so butterflies read LDS.
 template <typename R, int N>
@@ -250,11 +259,11 @@ __global__ void __launch_bounds__((ColCfg<N, R, SEG>::THREADS))
 }
 
 template <typename R, int N>
-__global__ void __launch_bounds__((ZCfg<N, R>::THREADS))
+__global__ void __launch_bounds__((ZWideCfg<N, R>::THREADS), (ZWideCfg<N, R>::LEAN ? 4 : 1))
     k_zinv_pupdate(ZPUpdateArgs a, const cplx<R>* __restrict__ twg) {
   constexpr int NC = 3;
   if (a.sv->done) return;
-  using Cfg = ZCfg<N, R>;
+  using Cfg = ZWideCfg<N, R>;
   constexpr int TP = Cfg::TP, TC = Cfg::TC;
   constexpr long long C = N / 2;
   constexpr long long S = (long long)N * N * C;
@@ -268,46 +277,52 @@ __global__ void __launch_bounds__((ZCfg<N, R>::THREADS))
   const int t = tid / TC;
   const int kx = blockIdx.x * TC + col;
   const int ky = wavenum<N>(blockIdx.y);
-  const long long base = (long long)blockIdx.y * C + kx;
+  // block-uniform bases and a 32-bit lane offset, as in k_xelast
+  const int lane = (int)blockIdx.y * (int)C + kx + t * (int)astride;
   const LdsView<R> lds{sbuf + col, TC, 1};
   const R beta = R(a.sv->beta);
   const R alpha = R(a.sv->alpha);
   const cplx<R>* __restrict__ r = static_cast<const cplx<R>*>(a.r);
-  cplx<R>* __restrict__ p = static_cast<cplx<R>*>(a.p);
+  cplx<R>* p = static_cast<cplx<R>*>(a.p);
   cplx<R>* __restrict__ x = static_cast<cplx<R>*>(a.x);
   cplx<R> pn[NC][8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const int n = t + TP * j;
-    const long long idx = base + (long long)n * astride;
+    const long long at = TP * j * astride;
     cplx<R> rv[NC], zv[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) rv[c] = r[c * S + idx];
+    for (int c = 0; c < NC; ++c) rv[c] = (r + c * S + at)[lane];
     apply_prec<R, NC>(rv, zv, kx, ky, wavenum<N>(n), a.cs, a.pc);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      const cplx<R> pv = p[c * S + idx];
+      const cplx<R> pv = (p + c * S + at)[lane];
       if (x) {
-        cplx<R> xv = x[c * S + idx];
+        cplx<R> xv = (x + c * S + at)[lane];
         xv.x += alpha * pv.x;
         xv.y += alpha * pv.y;
-        x[c * S + idx] = xv;
+        (x + c * S + at)[lane] = xv;
       }
       pn[c][j] = {zv[c].x + beta * pv.x, zv[c].y + beta * pv.y};
-      p[c * S + idx] = pn[c][j];
+      (p + c * S + at)[lane] = pn[c][j];
     }
+    if constexpr (Cfg::LEAN) hold_loads();
   }
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
 #pragma unroll
     for (int d = 0; d < 2; ++d) {
       cplx<R> acc[8];
+      if constexpr (Cfg::LEAN) hold_loads();
 #pragma unroll
-      for (int j = 0; j < 8; ++j) acc[j] = d ? ciw(pn[c][j], R(wavenum<N>(t + TP * j))) : pn[c][j];
+      for (int j = 0; j < 8; ++j) {
+        const cplx<R> v = Cfg::LEAN ? (p + c * S + TP * j * astride)[lane] : pn[c][j];
+        acc[j] = d ? ciw(v, R(wavenum<N>(t + TP * j))) : v;
+      }
       fft_block<R, N, true, 1>(acc, lds, t, tw);
       cplx<R>* __restrict__ dst = static_cast<cplx<R>*>(a.out[2 * c + d]);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) dst[base + (long long)(t + TP * j) * astride] = acc[j];
+      for (int j = 0; j < 8; ++j) (dst + TP * j * astride)[lane] = acc[j];
     }
   }
 }
@@ -441,9 +456,12 @@ __global__ void __launch_bounds__((ZCfg<N, R>::THREADS))
       if (c < 2) load_col(nxt, a.in[c + 1]);
     }
     fft_block<R, N, false, 1>(w, lds, t, tw);
-    if constexpr (!AHEAD) load_r();
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
+      if constexpr (!AHEAD) {
+        if (j % 2 == 0) hold_loads();
+        rv[j] = (r + c * S + TP * j * astride)[lane];
+      }
       const cplx<R> q = csub(u[j], ciw(w[j], R(wavenum<N>(t + TP * j))));
       rv[j].x -= alpha * q.x;
       rv[j].y -= alpha * q.y;
@@ -457,7 +475,7 @@ __global__ void __launch_bounds__((ZCfg<N, R>::THREADS))
   const ElastMeans em(a.cs);
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
-    if (j % 4 == 0) hold_loads();
+    if (j % (AHEAD ? 4 : 2) == 0) hold_loads();
     cplx<R> rv[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) rv[c] = (r + c * S + TP * j * astride)[lane];
@@ -1197,7 +1215,10 @@ void launch_zinv_pupdate(int n, const ZPUpdateArgs& a, const void* tw, hipStream
     using Cfg = ZCfg<NN, R>;
     dim3 grid((NN / 2) / Cfg::TC, NN, a.nsys > 0 ? a.nsys : 1);
     if (a.nsys > 0) hipLaunchKernelGGL((k_zinv_pupdate_b<R, NN>), grid, dim3(Cfg::THREADS), 0, st, a, twp);
-    else if constexpr (!tile_grid(NN)) hipLaunchKernelGGL((k_zinv_pupdate<R, NN>), grid, dim3(Cfg::THREADS), 0, st, a, twp);
+    else if constexpr (!tile_grid(NN)) {
+      using Z = ZWideCfg<NN, R>;
+      hipLaunchKernelGGL((k_zinv_pupdate<R, NN>), dim3((NN / 2) / Z::TC, NN), dim3(Z::THREADS), 0, st, a, twp);
+    }
     else no_elast_pass();
   });
 }
