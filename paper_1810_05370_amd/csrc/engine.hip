@@ -932,7 +932,8 @@ struct PlaneSolve {
     PrecBufs<R>& P = pb<R>(c);
     const double ab = double(c.V) * sizeof(R);  // one array
     const int kc = kcls<R>(TUMOR_K_KRYLOV64, TUMOR_K_KRYLOV32);
-    int most = 0, chunk = 1;
+    // (a count may be 2^31 - 1, the largest cap, so one more needs 64 bits)
+    long long most = 0, chunk = 1;
     bool any_fixed = false;
     for (int k = 0; k < ns; ++k) {
       a.thr2[k] = thr2[k];
@@ -944,11 +945,11 @@ struct PlaneSolve {
       if (!(active & (1 << k))) continue;
       // one launch more than the iterations: an iteration's residual is tested
       // at the start of the next one
-      most = std::max(most, limit[k] + 1);
+      most = std::max(most, limit[k] + 1LL);
       any_fixed = any_fixed || fixed[k];
-      chunk = std::max(chunk, std::min(limit[k], pred[k]) + 1);
+      chunk = std::max(chunk, std::min(limit[k], pred[k]) + 1LL);
     }
-    if (any_fixed) chunk = std::min(most, 64);
+    if (any_fixed) chunk = std::min(most, 64LL);
     launched = 0;
     tumor::launch_plane_start<R>(c.n, elast, r64, scale, active, a, slot(0), c.st);
     {
@@ -963,7 +964,7 @@ struct PlaneSolve {
     BatchScope scope(c, elast ? 0 : ns, elast ? 0 : __builtin_popcount((unsigned)active));
     c.batch_ns = elast ? 0 : ns;
     for (;;) {
-      for (int k = 0; k < chunk && launched < most; ++k, ++launched) {
+      for (long long k = 0; k < chunk && launched < most; ++k, ++launched) {
         c.cur_tag = launched;
         a.sv = slot(launched);
         a.svn = slot(launched + 1);
@@ -985,17 +986,17 @@ struct PlaneSolve {
       HIPCHECK(hipMemcpyAsync(c.hsv, slot(launched), ns * sizeof(tumor::SolveScalars), hipMemcpyDeviceToHost, c.st));
       HIPCHECK(hipStreamSynchronize(c.st));
       bool all_done = true;
-      int left = 0;
+      long long left = 0;
       for (int k = 0; k < ns; ++k) {
         const tumor::SolveScalars& h = c.hsv[k];
         c.batch_it[k] = (active & (1 << k)) ? h.it : 0;
         if (!(active & (1 << k)) || h.done) continue;
         all_done = false;
-        left = std::max(left, std::min(more(h, thr2[k], rr0[k], fixed[k], limit[k]), limit[k] + 1 - h.it));
+        left = std::max(left, std::min(more(h, thr2[k], rr0[k], fixed[k], limit[k]), limit[k] + 1LL - h.it));
       }
       timers_flush(c, elast ? c.hsv[0].it : 0x7fffffff);
       if (all_done || launched >= most) break;
-      chunk = std::max(1, std::min(left, any_fixed ? 64 : 32));
+      chunk = std::max(1LL, std::min(left, any_fixed ? 64LL : 32LL));
     }
     c.batch_ns = 0;
     for (int k = 0; k < ns; ++k) {
@@ -1007,8 +1008,8 @@ struct PlaneSolve {
   }
 
   // launches still needed, from the residual reduction so far
-  static int more(const tumor::SolveScalars& h, double thr2, double rr0, bool fixed, int limit) {
-    if (fixed) return limit + 1 - h.it;
+  static long long more(const tumor::SolveScalars& h, double thr2, double rr0, bool fixed, int limit) {
+    if (fixed) return limit + 1LL - h.it;
     // h.rr is the residual before iteration h.it
     if (rr0 > 0.0 && h.it > 1 && h.rr > thr2 && h.rr < rr0 && std::isfinite(h.rr)) {
       const double per_it = std::log(h.rr / rr0) / (h.it - 1);
