@@ -825,10 +825,15 @@ __device__ __forceinline__ void xelast_rows(const XElastArgs& a, const cplx<R>* 
                       cz = {ez[j].x * invV, ez[j].y * invV};
         const cplx<R> lt = {l.x * (ax.x + by.x + cz.x), l.y * (ax.y + by.y + cz.y)};
         if constexpr (EN) {
-          const cplx<R> d2 = {R(2) * (ax.x * ax.x + by.x * by.x + cz.x * cz.x),
-                              R(2) * (ax.y * ax.y + by.y * by.y + cz.y * cz.y)};
-          en += (double)m.x * (double)d2.x + (double)m.y * (double)d2.y + (double)lt.x * (double)(ax.x + by.x + cz.x) +
-                (double)lt.y * (double)(ax.y + by.y + cz.y);
+          // (in FP64 from the operands' values, and with mu first: the squares of
+          // the strains alone would underflow for moduli above 1e16 in FP32)
+          auto two_mu = [](R m, R a, R b, R c) {
+            const double dm = 2.0 * (double)m;
+            return dm * (double)a * (double)a + dm * (double)b * (double)b + dm * (double)c * (double)c;
+          };
+          auto tr = [](R a, R b, R c) { return (double)a + (double)b + (double)c; };
+          en += two_mu(m.x, ax.x, by.x, cz.x) + two_mu(m.y, ax.y, by.y, cz.y) + (double)lt.x * tr(ax.x, by.x, cz.x) +
+                (double)lt.y * tr(ax.y, by.y, cz.y);
           pin(en);
         }
         stash[j * RC::THREADS + threadIdx.x] = {R(2) * m.x * ax.x + lt.x, R(2) * m.y * ax.y + lt.y};

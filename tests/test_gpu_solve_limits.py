@@ -1,5 +1,5 @@
 """Solves at the limits of what their entry points accept: the largest
-iteration cap."""
+iteration cap, very stiff tissue."""
 import pytest
 
 import paper_1810_05370_amd as tm
@@ -31,3 +31,28 @@ def test_the_largest_iteration_cap_is_a_cap_that_is_never_met(n, precision):
     assert a[3] > 3 and max(a[5]) > 1
     assert a[3:] == b[3:]
     assert all(torch.equal(x, y) for x, y in zip(a[:3], b[:3]))
+
+
+def _stiffer(k):
+    """The workload's parameters with every modulus and the screening times 2^k: the displacement of the same
+    force is that of k = 0 times 2^-k."""
+    P = synthetic.params()
+    for name in ("lame_scale", "eta_tumor", "eta_healthy", "eta_bg"):
+        P[name] *= 2.0 ** k
+    return P
+
+
+@pytest.mark.parametrize("n", [16, 128, 256])
+def test_mixed_solve_does_not_depend_on_the_unit_of_the_moduli(n):
+    """Moduli 2^60 times as large.  The strains fit FP32 (about 1e-24 at 128^3), their squares do not.  The FP32
+    vectors are the same numbers with another exponent, but for values under 2^-126 (1e-14 of the largest), so
+    the iterations agree; one more is left to a residual that close to its threshold."""
+    need_gpu()
+    its = []
+    for k in (0, 60):
+        sim = _sim(n, "mixed", _stiffer(k))
+        u, it, rr = sim.solve_elasticity()   # (an error if the FP64 residual misses rtol)
+        sim.close()
+        its.append(it)
+        say(f"n={n}, moduli * 2^{k}: {it} iterations, residual {rr:.2e}, |u| {float(u.norm()):.3e}")
+    assert abs(its[1] - its[0]) <= 1
