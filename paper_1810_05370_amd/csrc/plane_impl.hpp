@@ -313,6 +313,8 @@ __global__ void __launch_bounds__(256) k_plane_xelast(PlaneArgs a, const cplx<R>
 
 // The iteration's scalars from gamma, ||r||^2 and delta; false: no update.
 // Every block computes them from the same totals; the first one stores them.
+// As on the larger grids, the first gamma has to be positive (an indefinite
+// preconditioner is refused) and every curvature.
 __device__ __forceinline__ bool plane_scalars(const SolveScalars& s, double gamma, double rr, double delta, double thr2,
                                               int limit, int fixed, SolveScalars* out, bool store, double& alpha,
                                               double& beta) {
@@ -322,7 +324,7 @@ __device__ __forceinline__ bool plane_scalars(const SolveScalars& s, double gamm
   const double den = s.it > 0 ? delta - beta * gamma / s.alpha : delta;
   alpha = gamma / den;
   bool go = false;
-  if (!(isfinite(gamma) && isfinite(rr) && isfinite(delta))) {
+  if (!(isfinite(gamma) && isfinite(rr) && isfinite(delta)) || (s.it == 0 && !(gamma > 0.0))) {
     n.bad = 1;
     n.done = 1;
   } else if (!fixed && rr <= thr2) {

@@ -1,5 +1,7 @@
 """Solves at the limits of what their entry points accept: the largest
-iteration cap, very stiff tissue."""
+iteration cap, very stiff tissue, an indefinite preconditioner."""
+import ctypes
+
 import pytest
 
 import paper_1810_05370_amd as tm
@@ -56,3 +58,27 @@ def test_mixed_solve_does_not_depend_on_the_unit_of_the_moduli(n):
         its.append(it)
         say(f"n={n}, moduli * 2^{k}: {it} iterations, residual {rr:.2e}, |u| {float(u.norm()):.3e}")
     assert abs(its[1] - its[0]) <= 1
+
+
+# (grid, nu and E of the CSF, screening): a negative modulus that makes the mean material, and so the
+# preconditioner, indefinite for the force, while the curvature along M^-1 r is positive
+INDEFINITE = [(16, 0.441, -3997.0, 13597.0), (32, 0.4083, -5610.0, 22977.0), (64, 0.41811, -6532.7, 25278.0),
+              (128, 0.4737, -1817.0, 261.0)]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n,nu,E,eta", INDEFINITE)
+def test_an_indefinite_preconditioner_is_refused_at_the_start(n, nu, E, eta, precision):
+    """<r, M^-1 r> < 0 at the start: TUMOR_ENAN before any iteration, the start vector unchanged."""
+    torch = need_gpu()
+    sim = _sim(n, precision, synthetic.params(nu_csf=nu, E_csf=E, eta_healthy=eta))
+    b = -sim.apply_op("force", sim.get("p"))
+    z = sim.apply_op("elast_precond", b)
+    gamma, curv = float((b * z).sum()), float((z * sim.apply_op("elasticity", z)).sum())
+    say(f"n={n} {precision}: <r, M^-1 r> = {gamma:.3e}, curvature {curv:.3e}")
+    assert gamma < 0.0 < curv
+    u, it, rr = torch.full((3, n, n, n), -1.0, dtype=torch.float64, device="cuda"), ctypes.c_int32(-1), ctypes.c_double(0)
+    code = sim.lib.tumor_solve_elasticity(sim.ctx, None, tm._ptr(u), ctypes.byref(it), ctypes.byref(rr))
+    sim.close()
+    assert code == tm.ENAN
+    assert it.value == 0 and not u.any()
