@@ -481,7 +481,7 @@ __global__ void __launch_bounds__((ZCfg<N, R>::THREADS))
     for (int c = 0; c < 3; ++c) rv[c] = (r + c * S + TP * j * astride)[lane];
     const int kz = wavenum<N>(t + TP * j), kxo = opaque(kx);
     double ia, f;
-    elast_prec_coefs((double)(kxo * kxo + ky * ky + kz * kz), em, ia, f);
+    elast_prec_coefs<R>((double)(kxo * kxo + ky * ky + kz * kz), em, ia, f);
     const R wk[3] = {R(kx), R(ky), R(kz)}, ff = R(f), fia = R(ia);
     const cplx<R> wr = {wk[0] * rv[0].x + wk[1] * rv[1].x + wk[2] * rv[2].x,
                         wk[0] * rv[0].y + wk[1] * rv[1].y + wk[2] * rv[2].y};

@@ -641,7 +641,7 @@ __global__ void __launch_bounds__(256) k_plane_start(const cplx<double>* r64, Pl
     const int ky = wavenum<N>(zy % N), kz = wavenum<N>(zy / N);
     const double w2 = (double)(kx * kx + ky * ky + kz * kz);
     double ia, f = 0.0;
-    if (nsv == 0) elast_prec_coefs(w2, ElastMeans(cs), ia, f);
+    if (nsv == 0) elast_prec_coefs<R>(w2, ElastMeans(cs), ia, f);
     else ia = 1.0 / (1.0 + h * cs->Kbar * w2);
     prec[(long long)kx * N * N + zy] = {R(ia), R(f)};
   }

@@ -1009,7 +1009,7 @@ __global__ void __launch_bounds__(kRedThreads) k_tile_start(const cplx<double>* 
     const long long e = ((long long)iz * N + iy) * Q::C + kx;
     const R wk[3] = {R(kx), R(ky), R(kz)};
     double ia, f;
-    elast_prec_coefs((double)(kx * kx + ky * ky + kz * kz), em, ia, f);
+    elast_prec_coefs<R>((double)(kx * kx + ky * ky + kz * kz), em, ia, f);
     const R ff = R(f), fia = R(ia);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {

@@ -6,18 +6,30 @@
 namespace tumor {
 
 // The elasticity inverse's two coefficients (below), 1/a and c / (a + c |w|^2),
-// from one division and without a branch; m: the coefficient means.
+// from one division by a d and without a branch; m: the coefficient means.  For
+// FP64 vectors the factors are first scaled (exactly) by the exponent of a: a d is
+// out of range beyond moduli of 1e154 (or 1e-154).  FP32 vectors' coefficients, below
+// 1e38, keep it in range.
 struct ElastMeans {
   double eta, mu, c;
   __device__ __forceinline__ explicit ElastMeans(const CoefScalars* cs)
       : eta(cs->etabar), mu(cs->mubar), c(cs->lambar + cs->mubar) {}
 };
+template <typename R>
 __device__ __forceinline__ void elast_prec_coefs(double w2, const ElastMeans& m, double& ia, double& f) {
-  const double a = m.eta + m.mu * w2;
-  const double d = a + m.c * w2;
-  const double inv = 1.0 / (a > 0.0 ? a * d : 1.0);
-  ia = a > 0.0 ? d * inv : 0.0;
-  f = m.c * a * inv;
+  double a = m.eta + m.mu * w2;
+  double d = a + m.c * w2, c = m.c;
+  const bool ok = a > 0.0;
+  int e = 0;
+  if constexpr (sizeof(R) == 8) {
+    a = frexp(a, &e);
+    d = ldexp(d, -e);
+    c = ldexp(c, -e);
+  }
+  const double inv = 1.0 / (ok ? a * d : 1.0);
+  ia = ok ? d * inv : 0.0;
+  if constexpr (sizeof(R) == 8) ia = ldexp(ia, -e);
+  f = c * a * inv;
 }
 
 // Constant-coefficient inverses per Fourier mode (integer wave numbers

@@ -176,7 +176,7 @@ __global__ void __launch_bounds__((TileCfg<R, N>::TA), (sizeof(R) == 4 ? 4 : 2))
       const R wk[3] = {fkx, R(ky(e)), fkz};
       const int kzo = opaque(kz);
       double ia, f;
-      elast_prec_coefs((double)(th.kx * th.kx + ky(e) * ky(e) + kzo * kzo), em, ia, f);
+      elast_prec_coefs<R>((double)(th.kx * th.kx + ky(e) * ky(e) + kzo * kzo), em, ia, f);
       cplx<R> rv[3];
 #pragma unroll
       for (int c = 0; c < 3; ++c) rv[c] = at(a.r, c, e)[tid];
@@ -316,7 +316,7 @@ __global__ void __launch_bounds__((TileCfg<R, N>::TA), (sizeof(R) == 4 ? 4 : 2))
     if (e % 4 == 0) hold_loads();
     const int kzo = opaque(kz);
     double ia, f;
-    elast_prec_coefs((double)(th.kx * th.kx + ky(e) * ky(e) + kzo * kzo), em, ia, f);
+    elast_prec_coefs<R>((double)(th.kx * th.kx + ky(e) * ky(e) + kzo * kzo), em, ia, f);
     cplx<R> rv[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) rv[c] = at(a.r, c, e)[tid];

@@ -1,5 +1,5 @@
 """Solves at the limits of what their entry points accept: the largest
-iteration cap, very stiff tissue, an indefinite preconditioner."""
+iteration cap, very stiff or soft tissue, an indefinite preconditioner."""
 import ctypes
 
 import pytest
@@ -82,3 +82,20 @@ def test_an_indefinite_preconditioner_is_refused_at_the_start(n, nu, E, eta, pre
     sim.close()
     assert code == tm.ENAN
     assert it.value == 0 and not u.any()
+
+
+@pytest.mark.parametrize("k", [600, -600])
+@pytest.mark.parametrize("n", [16, 64, 128, 256])
+def test_fp64_solve_scales_exactly_with_the_moduli(n, k):
+    """Powers of two are exact, so the solution is that of k = 0 times 2^-k, bit for bit, and its products and
+    squares must all stay in range."""
+    torch = need_gpu()
+    got = []
+    for e in (0, k):
+        sim = _sim(n, "fp64", _stiffer(e))
+        u, it, rr = sim.solve_elasticity()
+        sim.close()
+        say(f"n={n}, moduli * 2^{e}: {it} iterations, residual {rr:.2e}")
+        got.append((u * 2.0 ** e, it, rr))
+    assert got[0][1:] == got[1][1:]
+    assert torch.equal(got[0][0], got[1][0])
