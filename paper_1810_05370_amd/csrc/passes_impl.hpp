@@ -115,7 +115,9 @@ __device__ __forceinline__ void block_totals(double (&v)[NV], double* sh) {
 
 // alpha = rho / <p, A p> from nb parts (every block totals them in the same
 // order); the lead block publishes it, or the breakdown (alpha 0: nothing left
-// for the deferred x update to add).
+// for the deferred x update to add).  `done` stays as it is: the other blocks'
+// waves may not have read it yet, and a block must leave as a whole.  fin_update
+// sets it.
 template <int TH>
 __device__ __forceinline__ bool block_alpha(SolveScalars* sv, const double* part, int nb, bool lead, double* sh,
                                             double& alpha) {
@@ -127,10 +129,7 @@ __device__ __forceinline__ bool block_alpha(SolveScalars* sv, const double* part
   if (lead && threadIdx.x == 0) {
     sv->pq = tot[0];
     sv->alpha = alpha;
-    if (!ok) {
-      sv->bad = 1;
-      sv->done = 1;
-    }
+    if (!ok) sv->bad = 1;
   }
   return ok;
 }

@@ -869,8 +869,18 @@ __global__ void __launch_bounds__(kRedThreads) k_pcg_start(KrylovArgs a, SpecIdx
   block_store_partials<1>(acc, a.partials);
 }
 
-// After an update: iteration count, ||r||^2, convergence, beta and rho.
-__device__ __forceinline__ void fin_update(SolveScalars* sv, const double (&tot)[2], double thr2, int limit, int fixed) {
+// After an update (nb tiles' partials, two each): iteration count, ||r||^2,
+// convergence, beta and rho.  After a breakdown there was no update: the solve ends.
+__device__ __forceinline__ void fin_update(SolveScalars* sv, const double* part, int nb, double thr2, int limit,
+                                           int fixed) {
+  if (sv->done) return;
+  if (sv->bad) {
+    if (threadIdx.x == 0) sv->done = 1;
+    return;
+  }
+  double tot[2];
+  total_partials<2>(tot, part, nb, 2);
+  if (threadIdx.x != 0) return;
   sv->it += 1;
   sv->rr = tot[0];
   if (!(isfinite(tot[0]) && isfinite(tot[1]))) {
@@ -889,10 +899,7 @@ __device__ __forceinline__ void fin_update(SolveScalars* sv, const double (&tot)
 }
 
 __global__ void __launch_bounds__(kRedThreads) k_fin_update(KrylovArgs a, int nb) {
-  if (a.sv->done) return;
-  double tot[2];
-  total_partials<2>(tot, a.partials, nb, 2);
-  if (threadIdx.x == 0) fin_update(a.sv, tot, a.thr2, a.limit, a.fixed);
+  fin_update(a.sv, a.partials, nb, a.thr2, a.limit, a.fixed);
 }
 
 // The x update of the last iteration that ran (earlier ones happen in the
@@ -1233,11 +1240,7 @@ __global__ void __launch_bounds__(kRedThreads) k_bfin_start(SolveScalars* sv, in
 // convergence, beta and rho.
 __global__ void __launch_bounds__(kRedThreads) k_bfin_update(BatchArgs a, int nb) {
   const int s = blockIdx.x;
-  SolveScalars* sv = a.sv + s;
-  if (sv->done) return;
-  double tot[2];
-  total_partials<2>(tot, a.partials + 2LL * nb * s, nb, 2);
-  if (threadIdx.x == 0) fin_update(sv, tot, a.thr2[s], a.limit[s], a.fixed[s]);
+  fin_update(a.sv + s, a.partials + 2LL * nb * s, nb, a.thr2[s], a.limit[s], a.fixed[s]);
 }
 
 // x_k += alpha_k p_k for the last iteration each system ran (none: no-op).

@@ -66,22 +66,39 @@ INDEFINITE = [(16, 0.441, -3997.0, 13597.0), (32, 0.4083, -5610.0, 22977.0), (64
               (128, 0.4737, -1817.0, 261.0)]
 
 
-@pytest.mark.parametrize("precision", ["fp64", "mixed"])
-@pytest.mark.parametrize("n,nu,E,eta", INDEFINITE)
-def test_an_indefinite_preconditioner_is_refused_at_the_start(n, nu, E, eta, precision):
-    """<r, M^-1 r> < 0 at the start: TUMOR_ENAN before any iteration, the start vector unchanged."""
+# the same with a positive <r, M^-1 r> and a negative curvature
+BREAKDOWN = [(16, 0.49, -500.0, 1e4), (128, 0.49, -700.0, 1e4), (256, 0.49, -700.0, 1e4)]
+
+
+def _refused(n, nu, E, eta, precision):
+    """Signs of <r, M^-1 r> and of the curvature along M^-1 r at the start of an elasticity solve that must end
+    with TUMOR_ENAN before any iteration, the start vector unchanged."""
     torch = need_gpu()
     sim = _sim(n, precision, synthetic.params(nu_csf=nu, E_csf=E, eta_healthy=eta))
     b = -sim.apply_op("force", sim.get("p"))
     z = sim.apply_op("elast_precond", b)
     gamma, curv = float((b * z).sum()), float((z * sim.apply_op("elasticity", z)).sum())
     say(f"n={n} {precision}: <r, M^-1 r> = {gamma:.3e}, curvature {curv:.3e}")
-    assert gamma < 0.0 < curv
     u, it, rr = torch.full((3, n, n, n), -1.0, dtype=torch.float64, device="cuda"), ctypes.c_int32(-1), ctypes.c_double(0)
     code = sim.lib.tumor_solve_elasticity(sim.ctx, None, tm._ptr(u), ctypes.byref(it), ctypes.byref(rr))
     sim.close()
     assert code == tm.ENAN
     assert it.value == 0 and not u.any()
+    return gamma, curv
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n,nu,E,eta", INDEFINITE)
+def test_an_indefinite_preconditioner_is_refused_at_the_start(n, nu, E, eta, precision):
+    gamma, curv = _refused(n, nu, E, eta, precision)
+    assert gamma < 0.0 < curv
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n,nu,E,eta", BREAKDOWN)
+def test_a_negative_curvature_ends_the_solve(n, nu, E, eta, precision):
+    gamma, curv = _refused(n, nu, E, eta, precision)
+    assert curv < 0.0 < gamma
 
 
 @pytest.mark.parametrize("k", [600, -600])
