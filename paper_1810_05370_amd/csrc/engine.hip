@@ -781,7 +781,8 @@ int pcg_iterate(Ctx& c, tumor::KrylovArgs a, Apply apply, double thr2, int limit
       [&](int k) {
         Fuse fz{k > 0, a.r, a.x, a.sv, a.pc};
         apply(static_cast<const cplx<R>*>(a.p), static_cast<cplx<R>*>(a.q), &a.sv->done, &fz);
-        tumor::launch_fin_update(a, tumor::z_tiles<R>(c.n), c.st);
+        const int nb = tumor::z_tiles<R>(c.n);
+        timed(c, kc, 16.0 * nb, [&] { tumor::launch_fin_update(a, nb, c.st); });
       },
       thr2, limit, fixed, pred, conv, bad, rr0);
   timed(c, kc, 3.0 * vb, [&] { tumor::launch_pcg_xfinal<R>(a, c.st); });
@@ -861,7 +862,8 @@ struct TileSolve {
                 [&] { tumor::launch_tile_xelast<R>(c.n, xa, P.tw, c.st); });
           timed(c, kcls<R>(TUMOR_K_TILEFWD64, TUMOR_K_TILEFWD32), 14.0 * ab,
                 [&] { tumor::launch_tile_fwd<R>(c.n, fa, P.tw, c.st); });
-          tumor::launch_fin_update(ka, tumor::tile_fwd_blocks<R>(c.n), c.st);
+          const int nb = tumor::tile_fwd_blocks<R>(c.n);
+          timed(c, kc, 16.0 * nb, [&] { tumor::launch_fin_update(ka, nb, c.st); });
         },
         thr2, limit, fixed, pred, conv, bad, rr0);
   }
@@ -951,7 +953,10 @@ struct PlaneSolve {
     }
     if (any_fixed) chunk = std::min(most, 64LL);
     launched = 0;
-    tumor::launch_plane_start<R>(c.n, elast, r64, scale, active, a, slot(0), c.st);
+    // r64 in, r and the preconditioner out; each coefficient field in and out
+    const int nvec = elast ? 3 : __builtin_popcount((unsigned)active), ncoef = elast ? 3 : 1;
+    timed(c, kc, nvec * (8.0 * c.V + ab) + ab,
+          [&] { tumor::launch_plane_start<R>(c.n, elast, r64, scale, active, a, slot(0), c.st); });
     {
       const void* in[3] = {P.mu, P.lam, P.eta};
       void* out[3] = {const_cast<void*>(a.mu), const_cast<void*>(a.lam), const_cast<void*>(a.eta)};
@@ -959,7 +964,7 @@ struct PlaneSolve {
         in[0] = P.K;
         out[0] = out[1];
       }
-      tumor::launch_plane_coefs<R>(c.n, elast ? 3 : 1, in, out, c.st);
+      timed(c, kc, 2.0 * ncoef * ab, [&] { tumor::launch_plane_coefs<R>(c.n, ncoef, in, out, c.st); });
     }
     BatchScope scope(c, elast ? 0 : ns, elast ? 0 : __builtin_popcount((unsigned)active));
     c.batch_ns = elast ? 0 : ns;
@@ -1020,7 +1025,9 @@ struct PlaneSolve {
   }
 
   void finish(cplx<double>* x64, const double (&scale)[tumor::kMaxSys], int active) {
-    tumor::launch_plane_final<R>(c.n, elast, x64, scale, active, a, slot(launched), c.st);
+    const int nvec = elast ? 3 : __builtin_popcount((unsigned)active);
+    timed(c, kcls<R>(TUMOR_K_KRYLOV64, TUMOR_K_KRYLOV32), nvec * c.V * (16.0 + sizeof(R)),
+          [&] { tumor::launch_plane_final<R>(c.n, elast, x64, scale, active, a, slot(launched), c.st); });
   }
 };
 
@@ -1317,7 +1324,8 @@ void pcg_iterate_b(Ctx& c, tumor::BatchArgs a, const double* thr2, const int* li
       BFuse fz{launched == 0, a.r, a.x, a.sv, a.pc};
       diff_apply_b<R>(c, ns, static_cast<const cplx<R>*>(a.p), static_cast<cplx<R>*>(a.q), 1.0, -a.pc.h, skip,
                       &fz);
-      tumor::launch_bfin_update(a, tumor::z_tiles<R>(c.n), c.st);
+      const int nb = tumor::z_tiles<R>(c.n);
+      timed_b(c, kc, 0.0, 16.0 * nb, [&] { tumor::launch_bfin_update(a, nb, c.st); });
     }
     c.cur_tag = -1;
     HIPCHECK(hipGetLastError());
