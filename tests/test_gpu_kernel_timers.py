@@ -57,3 +57,28 @@ def test_an_elasticity_solve_is_timed_whole(n):
     assert it > 10
     for c in classes:
         assert [got[c]["launches"], got[c]["bytes"]] == want[c], c
+
+
+@pytest.mark.parametrize("n", [64, 128])
+def test_batched_diffusion_timers_count_each_system_while_it_iterates(n):
+    """Mixed: system k iterates it_diff[k] times in outer_diff[k] solves.  Per system and iteration the first
+    pass moves 5 arrays up to 64^3, 7 above (3 in a solve's first iteration, which takes p as it is), the x pass
+    6 with K once per launch, the last pass (above 64^3) 5."""
+    need_gpu()
+    sim = tm.from_inputs(synthetic.workload_inputs("seeds3_n128", n=n), synthetic.params(), precision="mixed")
+    sim.step(3)   # i and l nonzero: all three systems iterate
+    classes = ("zinvpb32", "xdiff32", "coldot32")
+    for c in classes:
+        sim.kernel_timer(c, True)
+    st = sim.step(1)
+    got = {c: sim.kernel_timer_read(c) for c in classes}
+    sim.close()
+    say(f"n={n}: {got}, iterations {st['it_diff']}, solves {st['outer_diff']}, elasticity {st['it_elast']}")
+    its, outer = sum(st["it_diff"]), sum(st["outer_diff"])
+    A = 4 * n ** 3
+    assert min(st["it_diff"]) < max(st["it_diff"])
+    assert got["zinvpb32"]["bytes"] == A * (5 * its if n <= 64 else 7 * its - 4 * outer)
+    assert got["xdiff32"]["bytes"] == A * (6 * its + got["xdiff32"]["launches"])
+    assert got["xdiff32"]["launches"] == got["zinvpb32"]["launches"]
+    # (the elasticity's last pass is in the same class: 12 arrays)
+    assert got["coldot32"]["bytes"] == (0 if n <= 64 else A * (5 * its + 12 * st["it_elast"]))
