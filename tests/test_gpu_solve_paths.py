@@ -100,3 +100,82 @@ def test_diffusion_in_lockstep(n):
     # the residual after three iterations is a difference of terms about 1 / rr_ref
     # times its size, each rounded to 1e-16
     assert abs(rr - rr_ref) <= 1e-9 * rr_ref + 1e-13
+
+
+def _three_systems(n, seed, **params):
+    """Parameters, inputs and i, o, l in mid-simulation, each with its own spectrum (so its own iteration count)."""
+    inp = synthetic.workload_inputs("seeds3_n128", n=n)
+    fields = dict(i=0.3 * synthetic.random_field(n, seed, 1.0) ** 2, o=0.8 + 0.02 * synthetic.random_field(n, seed + 1, 2.0),
+                  l=0.05 * synthetic.random_field(n, seed + 2, 0.5) ** 2)
+    return synthetic.params(**params), inp, fields
+
+
+@pytest.mark.parametrize("forced", [(2, 4, 3), (3, 0, 5)])
+@pytest.mark.parametrize("n", [16, 32, 64, 128])
+def test_batched_diffusion_in_lockstep(n, forced):
+    """i, o and l as one batch; each ends at its own launch, or takes no part."""
+    import torch
+    need_gpu()
+    say(f"batched diffusion lockstep n={n}, iterations {forced}")
+    P, inp, fields = _three_systems(n, 40)
+    st = model.init_state(P, n, inp["wm"], inp["gm"], inp["csf"], inp["centers"], inp["sigmas"], inp["weights"])
+    st = model.State(st.grid, P, dict(st.f, **fields), st.u, st.u_prev)
+    ref = model.step(st, dict(advection=False, elasticity=False), forced=[*forced, 0])
+    sim = tm.from_inputs(inp, P, flags=tm.F_EDEMA)
+    for k, v in fields.items():
+        sim.set(k, torch.as_tensor(v))
+    sim.refresh()
+    sim.force_iterations([*forced, 0])
+    got = sim.step(1)
+    err = {k: rel_l2(sim.get(k).cpu().numpy(), st.f[k]) for k in ("p", "i", "o", "l")}
+    say(f"  relL2 {err}, residuals {got['relres_diff']} (oracle {ref['relres_diff']})")
+    sim.close()
+    assert tuple(got["it_diff"]) == forced
+    assert max(err.values()) < 1e-11
+    for rr, rr_ref in zip(got["relres_diff"], ref["relres_diff"]):
+        assert abs(rr - rr_ref) <= 1e-9 * rr_ref + 1e-13
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n", [32, 128])
+def test_batched_diffusion_meets_its_tolerance(n, precision):
+    """With every reaction rate zero a step leaves the solutions of the three systems in i, o and l."""
+    import torch
+    need_gpu()
+    rates = ("rho_w", "rho_g", "alpha0", "beta0", "gamma", "delta_s", "delta_p", "delta_e", "delta_l")
+    P, inp, fields = _three_systems(n, 50, **{k: 0.0 for k in rates})
+    sim = tm.from_inputs(inp, P, precision=precision, flags=tm.F_EDEMA)
+    for k, v in fields.items():
+        sim.set(k, torch.as_tensor(v))
+    sim.refresh()
+    got = sim.step(1)
+    g, K = Grid(n), P["k_w"] * inp["wm"] + P["k_g"] * inp["gm"] + P["k_f"] * inp["csf"]
+    rel = []
+    for k in ("i", "o", "l"):
+        rhs = solvers.cn_rhs(g, K, 0.01, fields[k])
+        rel.append(norm(rhs - solvers.cn_matrix(g, K, 0.01, sim.get(k).cpu().numpy())) / norm(rhs))
+    say(f"batched diffusion n={n} {precision}: {got['it_diff']} iterations, residuals {got['relres_diff']}, by the oracle {rel}")
+    sim.close()
+    assert min(got["it_diff"]) < max(got["it_diff"])
+    for a, b in zip(rel, got["relres_diff"]):
+        assert a <= 1.01e-8 and abs(a - b) <= 1e-10
+
+
+@pytest.mark.parametrize("n", [32, 64])
+def test_one_diffusion_system_in_lockstep(n):
+    need_gpu()
+    say(f"one diffusion system n={n}")
+    inp = synthetic.workload_inputs("seeds3_n128", n=n)
+    P = synthetic.params()
+    st = model.init_state(P, n, inp["wm"], inp["gm"], inp["csf"], inp["centers"], inp["sigmas"], inp["weights"])
+    ref = model_single.step(st, dict(advection=False, elasticity=False), forced=[4, 0, 0, 0])
+    sim = tm.from_inputs(inp, P, model="single", flags=0)
+    sim.force_iterations([4, 0, 0, 0])
+    got = sim.step(1)
+    err = rel_l2(sim.get("p").cpu().numpy(), st.f["p"])
+    rr, rr_ref = got["relres_diff"][0], ref["relres_diff"][0]
+    say(f"  relL2 {err:.2e}, residual {rr:.3e} (oracle {rr_ref:.3e})")
+    sim.close()
+    assert got["it_diff"][0] == 4
+    assert err < 1e-11
+    assert abs(rr - rr_ref) <= 1e-9 * rr_ref + 1e-13
