@@ -179,3 +179,79 @@ def test_one_diffusion_system_in_lockstep(n):
     assert got["it_diff"][0] == 4
     assert err < 1e-11
     assert abs(rr - rr_ref) <= 1e-9 * rr_ref + 1e-13
+
+
+def test_elasticity_at_512_meets_its_tolerance():
+    """Random tissue (every mode takes part), both precisions.  The residual is taken by the FP64 operator of the
+    unfused passes, which test_gpu_maxsize.py checks on plane waves, so none of the solves' fused kernels judges
+    itself.  Its rounding, about 1e-16 of ||A|| ||u||, stays under 1e-10 of ||f||."""
+    torch = need_gpu()
+    n = 512
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(8)
+    w = 0.3 + 0.4 * torch.rand((n, n, n), generator=gen, dtype=torch.float64, device="cuda")
+    g = 0.1 + 0.1 * torch.rand((n, n, n), generator=gen, dtype=torch.float64, device="cuda")
+    c = 1.0 - w - g
+    centers, sigmas, weights = synthetic.tumor_seeds("three", 1)
+    sols = {}
+    for precision in ("mixed", "fp64"):
+        sim = tm.Tumor(n, synthetic.params(), w, g, c, centers, sigmas, weights, precision=precision)
+        say(f"512^3 elasticity, {precision}")
+        sols[precision] = sim.solve_elasticity()
+        say(f"  {sols[precision][1]} iterations, residual {sols[precision][2]:.3e}")
+        if precision == "mixed":
+            sim.close()
+            del sim
+            torch.cuda.empty_cache()
+    f = sim.apply_op("force", sim.get("p") + sim.get("n"))
+    for precision, (u, it, rr) in sols.items():
+        rel = float((f + sim.apply_op("elasticity", u)).norm() / f.norm())
+        say(f"  {precision}: by the unfused operator {rel:.3e}")
+        assert it > 5
+        assert rel <= 1.01e-8 and abs(rel - rr) <= 1e-10
+    sim.close()
+
+
+@pytest.mark.parametrize("n", [256, 512])
+def test_batched_diffusion_of_large_grids_meets_its_tolerance(n):
+    """As test_batched_diffusion_meets_its_tolerance, judged on the device by the FP64 operator of the unfused
+    passes with the coefficients the solve had."""
+    torch = need_gpu()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9)
+
+    def rand(lo, hi):
+        return lo + (hi - lo) * torch.rand((n, n, n), generator=gen, dtype=torch.float64, device="cuda")
+    w, g = rand(0.3, 0.7), rand(0.1, 0.2)
+    x = torch.arange(n, dtype=torch.float64, device="cuda") * (2.0 * np.pi / n)
+    # (a smooth field, a rough one and one in between: three iteration counts)
+    fields = dict(i=rand(0.0, 0.3), o=0.8 + 0.1 * torch.cos(3.0 * x) * torch.ones_like(w),
+                  l=0.05 + 0.01 * torch.cos(9.0 * x)[:, None, None] + rand(0.0, 1e-4))
+    rates = ("rho_w", "rho_g", "alpha0", "beta0", "gamma", "delta_s", "delta_p", "delta_e", "delta_l")
+    P = synthetic.params(**{k: 0.0 for k in rates})
+    sols = {}
+    for precision in ("mixed", "fp64"):
+        sim = tm.Tumor(n, P, w, g, 1.0 - w - g, precision=precision, flags=tm.F_EDEMA)
+        for k, v in fields.items():
+            sim.set(k, v)
+        sim.refresh()
+        st = sim.step(1)
+        say(f"batched diffusion {n}^3 {precision}: {st['it_diff']} iterations, residuals {st['relres_diff']}")
+        sols[precision] = (st, [sim.get(k) for k in fields])
+        if precision == "mixed":
+            sim.close()
+            del sim
+            torch.cuda.empty_cache()
+    sim.set("w", w)
+    sim.set("g", g)
+    sim.refresh()
+    for precision, (st, out) in sols.items():
+        rel = []
+        for x0, x1 in zip(fields.values(), out):
+            rhs = x0 + 0.005 * sim.apply_op("diffusion", x0)
+            rel.append(float((rhs - x1 + 0.005 * sim.apply_op("diffusion", x1)).norm() / rhs.norm()))
+        say(f"  {precision}: by the unfused operator {rel}")
+        assert min(st["it_diff"]) < max(st["it_diff"])
+        for a, b in zip(rel, st["relres_diff"]):
+            assert a <= 1.01e-8 and abs(a - b) <= 1e-10
+    sim.close()
