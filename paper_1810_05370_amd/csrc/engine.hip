@@ -704,7 +704,7 @@ struct SolveOut {
 };
 
 template <typename R>
-tumor::KrylovArgs kargs(Ctx& c, int ncomp, cplx<R>* x, tumor::SolveScalars* sv, double h, int kind) {
+tumor::KrylovArgs kargs(Ctx& c, cplx<R>* x, tumor::SolveScalars* sv) {
   PrecBufs<R>& P = pb<R>(c);
   tumor::KrylovArgs a;
   std::memset(&a, 0, sizeof(a));
@@ -718,9 +718,6 @@ tumor::KrylovArgs kargs(Ctx& c, int ncomp, cplx<R>* x, tumor::SolveScalars* sv, 
   a.sv = sv;
   a.partials = c.partials;
   a.n = c.n;
-  a.ncomp = ncomp;
-  a.pc.h = h;
-  a.pc.kind = kind;
   a.scale32 = 1.0;
   return a;
 }
@@ -772,7 +769,7 @@ int pcg_iterate(Ctx& c, tumor::KrylovArgs a, Apply apply, double thr2, int limit
   a.limit = limit;
   a.fixed = fixed ? 1 : 0;
   const int kc = kcls<R>(TUMOR_K_KRYLOV64, TUMOR_K_KRYLOV32);
-  const double vb = double(a.ncomp) * double(c.V) * sizeof(R);  // one Krylov vector
+  const double vb = 3.0 * double(c.V) * sizeof(R);  // one Krylov vector
   timed(c, kc, (zero_x ? 3.0 : 2.0) * vb, [&] { tumor::launch_pcg_start<R>(a, zero_x, c.st); });
   // iteration k: p = M^-1 r + beta p in the first pass (k > 0), A p, alpha and the
   // update of r in the last
@@ -846,7 +843,7 @@ struct TileSolve {
     fa.epart = c.dpart;
     fa.r = r;
     fa.partials = c.partials;
-    tumor::KrylovArgs ka = kargs<R>(c, 3, x, sv, 0.0, tumor::PREC_ELAST);
+    tumor::KrylovArgs ka = kargs<R>(c, x, sv);
     ka.thr2 = thr2;
     ka.limit = limit;
     ka.fixed = fixed ? 1 : 0;
@@ -1031,14 +1028,14 @@ struct PlaneSolve {
   }
 };
 
-// Solve A x = b for a spectral system.  On entry x holds x0 and `resid0`
+// Solve the elasticity system A x = b (spectral).  On entry x holds x0 and `resid0`
 // computes r = b - A x0 (and b, norms) into the FP64 vectors.  For the mixed
 // precision the FP32 inner PCG corrects x in FP64 outer iterations.
 template <typename Apply64, typename Apply32, typename Resid64>
-SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cplx<double>* bvec, double rtol,
-                      int which, Apply64 A64, Apply32 A32, Resid64 resid0) {
+SolveOut solve_system(Ctx& c, cplx<double>* x, cplx<double>* bvec, double rtol, int which, Apply64 A64, Apply32 A32,
+                      Resid64 resid0) {
   SolveOut so;
-  tumor::KrylovArgs a = kargs<double>(c, ncomp, x, c.sv64, h, kind);
+  tumor::KrylovArgs a = kargs<double>(c, x, c.sv64);
   a.b = bvec;
   resid0(a);
   readback(c, c.sv64);
@@ -1049,7 +1046,7 @@ SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cp
     so.conv = false;
     return so;
   }
-  const long long cnt = 2LL * ncomp * c.S;  // reals
+  const long long cnt = 6 * c.S;  // reals
   if (bb == 0.0) {
     HIPCHECK(hipMemsetAsync(x, 0, cnt * sizeof(double), c.st));
     return so;
@@ -1062,8 +1059,8 @@ SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cp
     return so;
   }
   const int pred = c.pred[which >= 0 ? which : 3];
-  const bool tiled = kind == tumor::PREC_ELAST && tumor::tile_grid(c.n);
-  const bool planes = kind == tumor::PREC_ELAST && tumor::plane_grid(c.n);
+  const bool tiled = tumor::tile_grid(c.n);
+  const bool planes = tumor::plane_grid(c.n);
   constexpr double kOnes[tumor::kMaxSys] = {1.0, 1.0, 1.0};
   PrecBufs<double>& P64 = c.p64;
   if (!c.mixed) {
@@ -1089,7 +1086,7 @@ SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cp
   }
   // Mixed precision: x64 += PCG32(b - A64 x64) until the FP64 residual meets rtol.
   PrecBufs<float>& P = c.p32;
-  tumor::KrylovArgs a32 = kargs<float>(c, ncomp, P.x, c.sv32, h, kind);
+  tumor::KrylovArgs a32 = kargs<float>(c, P.x, c.sv32);
   // r32 = float(r64): rerun the residual kernel on r64 with no subtraction.
   tumor::KrylovArgs conv_args = a;
   conv_args.b = a.r;
@@ -1105,7 +1102,7 @@ SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cp
     const double sc = (rms > 0.0 && std::isfinite(rms)) ? std::ldexp(1.0, -std::ilogb(rms)) : 1.0;
     conv_args.scale32 = sc;
     if (!tiled && !planes)
-      timed(c, TUMOR_K_KRYLOV64, ncomp * c.V * (16.0 + 4.0),
+      timed(c, TUMOR_K_KRYLOV64, 3 * c.V * (16.0 + 4.0),
             [&] { tumor::launch_residual<double>(conv_args, P.r, c.st); });
     const double need = rtol * std::sqrt(bb / rr);
     const double in_rtol = std::max(1e-4, 0.3 * need);
@@ -1142,7 +1139,7 @@ SolveOut solve_system(Ctx& c, int ncomp, int kind, double h, cplx<double>* x, cp
     tumor::KrylovArgs ar = a;
     ar.b = bvec;
     ar.ax = c.p64.q;
-    timed(c, TUMOR_K_KRYLOV64, 3.0 * ncomp * c.V * 8.0, [&] { tumor::launch_residual<double>(ar, nullptr, c.st); });
+    timed(c, TUMOR_K_KRYLOV64, 9.0 * c.V * 8.0, [&] { tumor::launch_residual<double>(ar, nullptr, c.st); });
     readback(c, c.sv64);
     rr = c.hsv->rr;
     if (c.hsv->bad) {
@@ -1184,7 +1181,6 @@ tumor::BatchArgs bargs(Ctx& c, int ns, int active, cplx<R>* x, tumor::SolveScala
   a.ns = ns;
   a.active = active;
   a.pc.h = h;
-  a.pc.kind = tumor::PREC_DIFF;
   for (int k = 0; k < tumor::kMaxSys; ++k) a.scale32[k] = 1.0;
   return a;
 }
@@ -1576,7 +1572,7 @@ SolveOut elast_solve(Ctx& c, cplx<double>* x, int which) {
     timed(c, TUMOR_K_KRYLOV64, 9.0 * c.V * 8.0, [&] { tumor::launch_residual<double>(a, nullptr, c.st); });
     a.ax = nullptr;
   };
-  return solve_system(c, 3, tumor::PREC_ELAST, 0.0, x, c.b64, c.cfg.rtol_elast, which, A64, A32, r0);
+  return solve_system(c, x, c.b64, c.cfg.rtol_elast, which, A64, A32, r0);
 }
 
 void refresh(Ctx& c, int do_reaction, const double* const* in, double* const* out) {
@@ -1902,7 +1898,8 @@ void apply_op_t(Ctx& c, int op, const double* in, double* out) {
       tumor::launch_f32_to_f64(reinterpret_cast<const float*>(tmp), dst, V, c.st);
     }
   };
-  tumor::KrylovArgs ka = kargs<R>(c, 1, X, c.sv64, 0.5 * c.cfg.dt, tumor::PREC_DIFF);
+  tumor::KrylovArgs ka = kargs<R>(c, X, c.sv64);
+  ka.pc.h = 0.5 * c.cfg.dt;
   switch (op) {
     case TUMOR_OP_DERIV_X:
     case TUMOR_OP_DERIV_Y:
@@ -1917,7 +1914,7 @@ void apply_op_t(Ctx& c, int op, const double* in, double* out) {
       break;
     case TUMOR_OP_CN_PRECOND:
       fwd3<R>(c, in, nullptr, X);
-      tumor::launch_precond<R>(ka, X, Q, c.st);
+      tumor::launch_precond<R>(ka, 1, X, Q, c.st);
       to_out(Q, out, 1.0 / (double)V, -1);
       break;
     case TUMOR_OP_ELASTICITY:
@@ -1926,9 +1923,7 @@ void apply_op_t(Ctx& c, int op, const double* in, double* out) {
       if (op == TUMOR_OP_ELASTICITY) {
         elast_apply<R>(c, X, Q, nullptr);
       } else {
-        ka.ncomp = 3;
-        ka.pc.kind = tumor::PREC_ELAST;
-        tumor::launch_precond<R>(ka, X, Q, c.st);
+        tumor::launch_precond<R>(ka, 3, X, Q, c.st);
       }
       for (int k = 0; k < 3; ++k) to_out(Q + k * S, out + k * V, 1.0 / (double)V, -1);
       break;
@@ -2005,7 +2000,7 @@ SolveOut adjoint_solve(Ctx& c, const double* rhs, int which) {
   auto A32 = [&](const cplx<float>* p, cplx<float>* q, const int* skip, const Fuse* fz = nullptr) {
     elast_apply<float>(c, p, q, skip, fz);
   };
-  return solve_system(c, 3, tumor::PREC_ELAST, 0.0, x, c.b64, c.cfg.rtol_elast, which, A64, A32, r0);
+  return solve_system(c, x, c.b64, c.cfg.rtol_elast, which, A64, A32, r0);
 }
 
 // CN adjoint of one field, given y = A^-1 cbar_plus (spectral): out = (1 + dt/2 D) y;

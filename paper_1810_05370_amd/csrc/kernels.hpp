@@ -114,12 +114,9 @@ void launch_sl_tile(const SLArgs& a, CoefScalars* cs, hipStream_t st);
 void launch_interp(int n, const double* q, const double* jx, const double* jy, const double* jz,
                    long long count, double* out, hipStream_t st);
 
-// ---- Krylov vectors in spectral space (ncomp blocks of S = N^3/2 complex)
-enum PrecKind : int { PREC_DIFF = 0, PREC_ELAST = 1 };
-
+// ---- Krylov vectors of the elasticity in spectral space (three blocks of S = N^3/2 complex)
 struct PrecConsts {
   double h;  // dt/2 for CN
-  int kind;  // PrecKind
 };
 
 struct KrylovArgs {
@@ -128,7 +125,7 @@ struct KrylovArgs {
   const CoefScalars* cs;
   SolveScalars* sv;
   double* partials;
-  int n, ncomp;
+  int n;
   PrecConsts pc;
   double thr2;   // convergence threshold on ||r||^2
   int limit;     // iteration limit (max_it or a forced count)
@@ -150,15 +147,14 @@ void launch_fin_update(const KrylovArgs& a, int nb, hipStream_t st);
 // x += alpha p for the last iteration that ran (none: no-op)
 template <typename R>
 void launch_pcg_xfinal(const KrylovArgs& a, hipStream_t st);
-// out = M^-1 in (one application of the preconditioner)
+// out = M^-1 in (one application of the preconditioner: ncomp 1 diffusion, 3 elasticity)
 template <typename R>
-void launch_precond(const KrylovArgs& a, const void* in, void* out, hipStream_t st);
+void launch_precond(const KrylovArgs& a, int ncomp, const void* in, void* out, hipStream_t st);
 // ---- ns independent systems sharing one operator (the CN solves of i, o, l).
 // Vectors hold ns blocks of S complex values; system k has its own scalars
 // sv[k] and stopping rule (thr2, limit, fixed).  Only systems whose bit is set
 // in `active` are read or written; the finishing kernels mark the others done.
-// Each system's arithmetic (and the order of its sums) is that of the
-// one-system kernels above.
+// A system's arithmetic and the order of its sums do not depend on the others.
 struct BatchArgs {
   void *x, *r, *p, *q, *b;
   const void* ax;  // nullable (residual: r = b - ax)
@@ -166,7 +162,7 @@ struct BatchArgs {
   SolveScalars* sv;  // ns entries
   double* partials;
   int n, ns, active;
-  PrecConsts pc;  // PREC_DIFF
+  PrecConsts pc;
   double thr2[kMaxSys];
   int limit[kMaxSys];
   int fixed[kMaxSys];

@@ -296,12 +296,10 @@ __global__ void __launch_bounds__((ZWideCfg<N, R>::THREADS), (ZWideCfg<N, R>::LE
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const cplx<R> pv = (p + c * S + at)[lane];
-      if (x) {
-        cplx<R> xv = (x + c * S + at)[lane];
-        xv.x += alpha * pv.x;
-        xv.y += alpha * pv.y;
-        (x + c * S + at)[lane] = xv;
-      }
+      cplx<R> xv = (x + c * S + at)[lane];
+      xv.x += alpha * pv.x;
+      xv.y += alpha * pv.y;
+      (x + c * S + at)[lane] = xv;
       pn[c][j] = {zv[c].x + beta * pv.x, zv[c].y + beta * pv.y};
       (p + c * S + at)[lane] = pn[c][j];
     }

@@ -820,8 +820,9 @@ __device__ __forceinline__ double wdot(cplx<R> a, cplx<R> b, int kx) {
 }
 
 // r = b - ax (ax nullable); bb = ||b||^2, rr = ||r||^2 (Parseval-weighted).
-template <typename R, int NC>
+template <typename R>
 __global__ void __launch_bounds__(kRedThreads) k_residual(KrylovArgs a, SpecIdx ix, cplx<float>* r32) {
+  constexpr int NC = 3;
   const long long S = (long long)a.n * a.n * (a.n / 2);
   const cplx<R>* b = static_cast<const cplx<R>*>(a.b);
   const cplx<R>* ax = static_cast<const cplx<R>*>(a.ax);
@@ -844,8 +845,9 @@ __global__ void __launch_bounds__(kRedThreads) k_residual(KrylovArgs a, SpecIdx 
   block_store_partials<2>(acc, a.partials);
 }
 
-template <typename R, int NC>
+template <typename R>
 __global__ void __launch_bounds__(kRedThreads) k_pcg_start(KrylovArgs a, SpecIdx ix, int zero_x) {
+  constexpr int NC = 3;
   const long long S = (long long)a.n * a.n * (a.n / 2);
   const cplx<R>* r = static_cast<const cplx<R>*>(a.r);
   cplx<R>* p = static_cast<cplx<R>*>(a.p);
@@ -905,8 +907,9 @@ __global__ void __launch_bounds__(kRedThreads) k_fin_update(KrylovArgs a, int nb
 // The x update of the last iteration that ran (earlier ones happen in the
 // fused p-update pass of the next iteration).  Runs whatever `done` says; no
 // iteration ran when it == 0.
-template <typename R, int NC>
+template <typename R>
 __global__ void __launch_bounds__(256) k_pcg_xfinal(KrylovArgs a) {
+  constexpr int NC = 3;
   if (a.sv->it == 0) return;
   const long long S = (long long)a.n * a.n * (a.n / 2);
   const R alpha = R(a.sv->alpha);
@@ -939,18 +942,13 @@ __global__ void __launch_bounds__(256) k_precond(KrylovArgs a, SpecIdx ix, const
   for (int c = 0; c < NC; ++c) out[e + c * S] = zv[c];
 }
 
-#define TUMOR_NC_DISPATCH(nc, BODY)                    \
-  if ((nc) == 1) { constexpr int NCC = 1; BODY; }      \
-  else { constexpr int NCC = 3; BODY; }
-
 static inline long long spec_count(int n) { return (long long)n * n * (n / 2); }
 
 template <typename R>
 void launch_residual(const KrylovArgs& a, void* r32, hipStream_t st) {
   const SpecIdx ix = make_idx(a.n);
   const int nb = red_blocks(spec_count(a.n));
-  TUMOR_NC_DISPATCH(a.ncomp, hipLaunchKernelGGL((k_residual<R, NCC>), dim3(nb), dim3(kRedThreads), 0, st, a, ix,
-                                                 static_cast<cplx<float>*>(r32)));
+  hipLaunchKernelGGL((k_residual<R>), dim3(nb), dim3(kRedThreads), 0, st, a, ix, static_cast<cplx<float>*>(r32));
   hipLaunchKernelGGL(k_fin_resid, dim3(1), dim3(kRedThreads), 0, st, a.sv, a.partials, nb);
 }
 
@@ -958,8 +956,7 @@ template <typename R>
 void launch_pcg_start(const KrylovArgs& a, int zero_x, hipStream_t st) {
   const SpecIdx ix = make_idx(a.n);
   const int nb = red_blocks(spec_count(a.n));
-  TUMOR_NC_DISPATCH(a.ncomp, hipLaunchKernelGGL((k_pcg_start<R, NCC>), dim3(nb), dim3(kRedThreads), 0, st, a, ix,
-                                                 zero_x));
+  hipLaunchKernelGGL((k_pcg_start<R>), dim3(nb), dim3(kRedThreads), 0, st, a, ix, zero_x);
   hipLaunchKernelGGL(k_fin_start, dim3(1), dim3(kRedThreads), 0, st, a.sv, a.partials, nb);
 }
 
@@ -971,17 +968,17 @@ void launch_fin_update(const KrylovArgs& a, int nb, hipStream_t st) {
 template <typename R>
 void launch_pcg_xfinal(const KrylovArgs& a, hipStream_t st) {
   const long long S = spec_count(a.n);
-  TUMOR_NC_DISPATCH(a.ncomp, hipLaunchKernelGGL((k_pcg_xfinal<R, NCC>), dim3((unsigned)((S + 255) / 256)),
-                                                 dim3(256), 0, st, a));
+  hipLaunchKernelGGL((k_pcg_xfinal<R>), dim3((unsigned)((S + 255) / 256)), dim3(256), 0, st, a);
 }
 
 template <typename R>
-void launch_precond(const KrylovArgs& a, const void* in, void* out, hipStream_t st) {
+void launch_precond(const KrylovArgs& a, int ncomp, const void* in, void* out, hipStream_t st) {
   const SpecIdx ix = make_idx(a.n);
-  const long long S = spec_count(a.n);
-  TUMOR_NC_DISPATCH(a.ncomp, hipLaunchKernelGGL((k_precond<R, NCC>), dim3((unsigned)((S + 255) / 256)),
-                                                 dim3(256), 0, st, a, ix, static_cast<const cplx<R>*>(in),
-                                                 static_cast<cplx<R>*>(out)));
+  const dim3 grid((unsigned)((spec_count(a.n) + 255) / 256)), block(256);
+  const cplx<R>* ip = static_cast<const cplx<R>*>(in);
+  cplx<R>* op = static_cast<cplx<R>*>(out);
+  if (ncomp == 1) hipLaunchKernelGGL((k_precond<R, 1>), grid, block, 0, st, a, ix, ip, op);
+  else hipLaunchKernelGGL((k_precond<R, 3>), grid, block, 0, st, a, ix, ip, op);
 }
 
 // ------------------------------------- natural order <-> tile order (tile.hpp)
@@ -1114,7 +1111,7 @@ TUMOR_INST_TILE(double)
 TUMOR_INST_TILE(float)
 
 // ---------------------------------------------- batched independent systems
-// ns one-component systems (PREC_DIFF) sharing an operator: system k's
+// ns one-component systems (diffusion) sharing an operator: system k's
 // partials sit at slots k (and kMaxSys + k) of a block, its scalars in sv[k].
 // The per-system sums run over the same elements in the same order as the
 // one-system kernels, so each system's scalars equal its own solve's.
@@ -1324,16 +1321,17 @@ void launch_badd32to64(void* x64, const void* x32, const double (&s)[kMaxSys], i
 }
 
 #define TUMOR_INST_KRYLOV(R)                                                               \
-  template void launch_residual<R>(const KrylovArgs&, void*, hipStream_t);                 \
   template void launch_pcg_start<R>(const KrylovArgs&, int, hipStream_t);                  \
   template void launch_pcg_xfinal<R>(const KrylovArgs&, hipStream_t);                      \
-  template void launch_precond<R>(const KrylovArgs&, const void*, void*, hipStream_t);     \
-  template void launch_bresidual<R>(const BatchArgs&, void*, hipStream_t);                 \
-  template void launch_bcn_residual<R>(const BatchArgs&, const void*, const void*, hipStream_t); \
+  template void launch_precond<R>(const KrylovArgs&, int, const void*, void*, hipStream_t); \
   template void launch_bpcg_start<R>(const BatchArgs&, int, hipStream_t);                  \
   template void launch_bpcg_xfinal<R>(const BatchArgs&, hipStream_t);
 TUMOR_INST_KRYLOV(double)
 TUMOR_INST_KRYLOV(float)
+// (residuals are taken in FP64)
+template void launch_residual<double>(const KrylovArgs&, void*, hipStream_t);
+template void launch_bresidual<double>(const BatchArgs&, void*, hipStream_t);
+template void launch_bcn_residual<double>(const BatchArgs&, const void*, const void*, hipStream_t);
 
 // -------------------------------------------------------------- conversions
 __global__ void k_add32to64(double* x, const float* y, double s, long long count) {

@@ -127,7 +127,7 @@ struct TileThread {
 // registers would halve the waves, which measured slower.
 template <typename R, int N>
 __global__ void __launch_bounds__((TileCfg<R, N>::TA), (sizeof(R) == 4 ? 4 : 2)) k_tile_inv(TileInvArgs a, const cplx<R>* __restrict__ twg) {
-  if (a.sv && a.sv->done) return;
+  if (a.sv->done) return;
   using T = TileCfg<R, N>;
   constexpr long long S = (long long)N * N * (N / 2);
   __shared__ cplx<R> buf[T::LDSA];
@@ -348,7 +348,7 @@ __global__ void __launch_bounds__((TileCfg<R, N>::TA), (sizeof(R) == 4 ? 4 : 2))
 // the coefficient re-reads among them.
 template <typename R, int N>
 __global__ void __launch_bounds__((TileCfg<R, N>::TB), 2) k_tile_xelast(TileXArgs a, const cplx<R>* __restrict__ twg) {
-  if (a.sv && a.sv->done) return;
+  if (a.sv->done) return;
   using T = TileCfg<R, N>;
   constexpr bool RICH = sizeof(R) == 4;
   constexpr int L = T::L, LB = T::LB, YB = T::YB, NS = 16 / T::YB;
