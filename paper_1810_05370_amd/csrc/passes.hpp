@@ -33,12 +33,14 @@ constexpr int kMaxTerms = 3;
 constexpr int kSplitMaxN = 64;
 // Grids whose elasticity iteration runs on the two-kernel transforms (tile.hpp).
 // At 256^3 it moves 58 arrays instead of 89 (FP32 1.23 -> 1.13 ms, FP64 2.44 ->
-// 2.10).  A 128^3 grid's arrays stay in the 256 MB last-level cache, where the
-// saved passes bring nothing (FP32 0.18 -> 0.19 ms); a 512^3 tile does not fit
+// 2.10).  At 128^3 there are 128 (FP32) or 256 (FP64) spectral tiles for 256 CUs
+// and the FP64 x side keeps one wave per SIMD: a solve of 47 iterations takes 15.2
+// ms for 13.9 in FP64, one of 48 10.4 for 8.2 in FP32.  A 512^3 tile does not fit
 // LDS with 64-byte pieces.
 constexpr bool tile_grid(int n) { return n == 256; }
-// Grids whose Krylov iterations run in three kernels on kx planes (plane.hpp):
-// a plane of 128^2 no longer fits LDS.
+// Grids whose Krylov iterations run in three kernels on kx planes (plane.hpp),
+// 8 elements a thread: a plane of 128^2 would take 2048 threads, and in FP64 does
+// not fit LDS either (295 KB; in FP32 147 of 160 KB).
 constexpr bool plane_grid(int n) { return n <= 64; }
 
 enum ColSym : int { SYM_ONE = 0, SYM_IW = 1, SYM_RAW = 2 };

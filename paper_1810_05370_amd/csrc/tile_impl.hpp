@@ -122,9 +122,11 @@ struct TileThread {
 
 // ------------------------------------------------------------ spectral side
 // Memory bounds both spectral kernels (256^3, counted): inverse 26 arrays in
-// 0.70 ms (FP64) and 0.37 ms (FP32), 5.0 and 4.7 TB/s; forward 18 arrays in 0.58
-// and 0.37 ms.  One or two components of p and r are read twice: all three in
-// registers would halve the waves, which measured slower.
+// 0.70 ms (FP64) and 0.36 ms (FP32), 5.0 and 4.8 TB/s; forward 18 (FP32 21) arrays in
+// 0.59 and 0.36 ms, 4.0 TB/s.  One or two components of p and r are read
+// twice: all three in registers would halve the waves, which measured slower.  The
+// next half array's loads ahead of a transform spill in the forward kernel: 0.91
+// and 0.66 ms.
 template <typename R, int N>
 __global__ void __launch_bounds__((TileCfg<R, N>::TA), (sizeof(R) == 4 ? 4 : 2)) k_tile_inv(TileInvArgs a, const cplx<R>* __restrict__ twg) {
   if (a.sv->done) return;
@@ -344,7 +346,7 @@ __global__ void __launch_bounds__((TileCfg<R, N>::TA), (sizeof(R) == 4 ? 4 : 2))
 // ------------------------------------------------------------------ x side
 // Ten row transforms in and nine out per row.  FP32 (0.39 ms at 256^3) keeps mu,
 // eta and the next inputs in registers and is bound by its instructions and LDS
-// accesses; FP64 (0.82 ms) has no room for them and moves 32 arrays at 5 TB/s,
+// accesses; FP64 (0.83 ms) has no room for them and moves 33 arrays at 5.4 TB/s,
 // the coefficient re-reads among them.
 template <typename R, int N>
 __global__ void __launch_bounds__((TileCfg<R, N>::TB), 2) k_tile_xelast(TileXArgs a, const cplx<R>* __restrict__ twg) {
