@@ -137,7 +137,7 @@ struct XElastArgs {
   const void* lam;
   const void* eta;
   const int* skip;
-  double* epart;  // nullable: each row tile's part of <p, A p> (its energy times N^3)
+  double* epart;  // nullable: each row tile's part of <p, A p> (N^3 times its energy)
 };
 
 // Diffusion x pass for ns fields (systems) sharing K.  Inputs per field s:

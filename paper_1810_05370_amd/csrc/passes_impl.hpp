@@ -759,7 +759,10 @@ __global__ void __launch_bounds__(RowCfg<N>::THREADS) k_xfwd(XProg prog, const c
   }
 }
 
-// EN: also the energy sum of each row tile (XElastArgs.epart).
+// EN: also the energy sum of each row tile (XElastArgs.epart), N^3 times the
+// physical one: every stress (or eta u) with its strain (or u) as the transform
+// gives it, before the 1 / N^3, in FP64.  Products of two physical values are N^3
+// times smaller than those of spectral modes and underflow that much earlier.
 template <typename R, int N, bool EN>
 __device__ __forceinline__ void xelast_rows(const XElastArgs& a, const cplx<R>* __restrict__ twg) {
   if (a.skip && *a.skip) return;
@@ -818,24 +821,18 @@ __device__ __forceinline__ void xelast_rows(const XElastArgs& a, const cplx<R>* 
         const int p = t + TP * j;
         const cplx<R> m = mu[ro + p], l = lam[ro + p];
         ex[j] = stash[j * RC::THREADS + threadIdx.x];
-        const cplx<R> ax = {ex[j].x * invV, ex[j].y * invV}, by = {ey[j].x * invV, ey[j].y * invV},
-                      cz = {ez[j].x * invV, ez[j].y * invV};
-        const cplx<R> lt = {l.x * (ax.x + by.x + cz.x), l.y * (ax.y + by.y + cz.y)};
+        const cplx<R> a = ex[j], b = ey[j], d = ez[j];
+        const cplx<R> ax = {a.x * invV, a.y * invV}, by = {b.x * invV, b.y * invV}, dz = {d.x * invV, d.y * invV};
+        const cplx<R> lt = {l.x * (ax.x + by.x + dz.x), l.y * (ax.y + by.y + dz.y)};
+        const cplx<R> sx = {R(2) * m.x * ax.x + lt.x, R(2) * m.y * ax.y + lt.y};
+        ey[j] = {R(2) * m.x * by.x + lt.x, R(2) * m.y * by.y + lt.y};
+        ez[j] = {R(2) * m.x * dz.x + lt.x, R(2) * m.y * dz.y + lt.y};
         if constexpr (EN) {
-          // (in FP64 from the operands' values, and with mu first: the squares of
-          // the strains alone would underflow for moduli above 1e16 in FP32)
-          auto two_mu = [](R m, R a, R b, R c) {
-            const double dm = 2.0 * (double)m;
-            return dm * (double)a * (double)a + dm * (double)b * (double)b + dm * (double)c * (double)c;
-          };
-          auto tr = [](R a, R b, R c) { return (double)a + (double)b + (double)c; };
-          en += two_mu(m.x, ax.x, by.x, cz.x) + two_mu(m.y, ax.y, by.y, cz.y) + (double)lt.x * tr(ax.x, by.x, cz.x) +
-                (double)lt.y * tr(ax.y, by.y, cz.y);
+          en += (double)sx.x * (double)a.x + (double)sx.y * (double)a.y + (double)ey[j].x * (double)b.x +
+                (double)ey[j].y * (double)b.y + (double)ez[j].x * (double)d.x + (double)ez[j].y * (double)d.y;
           pin(en);
         }
-        stash[j * RC::THREADS + threadIdx.x] = {R(2) * m.x * ax.x + lt.x, R(2) * m.y * ax.y + lt.y};
-        ey[j] = {R(2) * m.x * by.x + lt.x, R(2) * m.y * by.y + lt.y};
-        ez[j] = {R(2) * m.x * cz.x + lt.x, R(2) * m.y * cz.y + lt.y};
+        stash[j * RC::THREADS + threadIdx.x] = sx;
       }
       asm volatile("" ::: "memory");
       row_r2c<R, N, HALF>(ez, lds, t, tw);
@@ -859,7 +856,7 @@ __device__ __forceinline__ void xelast_rows(const XElastArgs& a, const cplx<R>* 
       const cplx<R> v = ux[j];
       ux[j] = {e.x * v.x * invV, e.y * v.y * invV};
       if constexpr (EN) {
-        en += (double)ux[j].x * (double)(v.x * invV) + (double)ux[j].y * (double)(v.y * invV);
+        en += (double)ux[j].x * (double)v.x + (double)ux[j].y * (double)v.y;
         pin(en);
       }
     }
@@ -884,8 +881,8 @@ __device__ __forceinline__ void xelast_rows(const XElastArgs& a, const cplx<R>* 
       s[j] = {m.x * sv.x * invV, m.y * sv.y * invV};
       u[j] = {e.x * uv.x * invV, e.y * uv.y * invV};
       if constexpr (EN) {
-        en += (double)s[j].x * (double)(sv.x * invV) + (double)s[j].y * (double)(sv.y * invV) +
-              (double)u[j].x * (double)(uv.x * invV) + (double)u[j].y * (double)(uv.y * invV);
+        en += (double)s[j].x * (double)sv.x + (double)s[j].y * (double)sv.y + (double)u[j].x * (double)uv.x +
+              (double)u[j].y * (double)uv.y;
         pin(en);
       }
     }
@@ -906,7 +903,7 @@ __device__ __forceinline__ void xelast_rows(const XElastArgs& a, const cplx<R>* 
       const cplx<R> sv = s[j];
       s[j] = {m.x * sv.x * invV, m.y * sv.y * invV};
       if constexpr (EN) {
-        en += (double)s[j].x * (double)(sv.x * invV) + (double)s[j].y * (double)(sv.y * invV);
+        en += (double)s[j].x * (double)sv.x + (double)s[j].y * (double)sv.y;
         pin(en);
       }
     }
@@ -916,7 +913,7 @@ __device__ __forceinline__ void xelast_rows(const XElastArgs& a, const cplx<R>* 
   if constexpr (EN) {
     static_assert(RC::THREADS == 64, "one wave per block");
     en = wave_sum_f(en);
-    if (threadIdx.x == 0) a.epart[row_tile()] = en * ((double)N * N * N);
+    if (threadIdx.x == 0) a.epart[row_tile()] = en;
   }
 }
 

@@ -265,9 +265,7 @@ __global__ void __launch_bounds__(256) k_plane_xelast(PlaneArgs a, const cplx<R>
   hold_loads();
   if (a.sv->done) return;
   __syncthreads();
-  rw.c2r(v, A, B, stw);
-#pragma unroll
-  for (int j = 0; j < 8; ++j) v[j] = {v[j].x * invV, v[j].y * invV};
+  rw.c2r(v, A, B, stw);  // N^3 times the strain or displacement
   // the trace: the diagonal strains pass through the waves' row buffers
   cplx<R>* mine = buf[wv];
   wave_sync();
@@ -287,7 +285,11 @@ __global__ void __launch_bounds__(256) k_plane_xelast(PlaneArgs a, const cplx<R>
       w[j] = {R(2) * w[j].x + l[j].x * (e0.x + e1.x + e2.x), R(2) * w[j].y + l[j].y * (e0.y + e1.y + e2.y)};
     }
   }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) w[j] = {w[j].x * invV, w[j].y * invV};
   if (role < 9) {
+    // <z, A z> of the spectral vectors is N^3 times the physical sum (and products of
+    // two physical values would underflow N^3 times as early)
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[0] += pdot(w[j], v[j]);
   }
@@ -307,8 +309,7 @@ __global__ void __launch_bounds__(256) k_plane_xelast(PlaneArgs a, const cplx<R>
   }
   if (role != 0 && role < 9) rw.store(half(dst[role]), w);
   plane_totals<1, 256>(acc, sh);
-  // <z, A z> of the spectral vectors is N^3 times the physical sum
-  if (threadIdx.x == 0) a.epart[blockIdx.y * T::NX + blockIdx.x] = acc[0] * ((double)N * N * N);
+  if (threadIdx.x == 0) a.epart[blockIdx.y * T::NX + blockIdx.x] = acc[0];
 }
 
 // The iteration's scalars from gamma, ||r||^2 and delta; false: no update.
@@ -543,9 +544,9 @@ __global__ void __launch_bounds__(64) k_plane_xdiff(PlaneArgs a, const cplx<R>* 
   double acc[1] = {0.0};
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
-    const cplx<R> e = {v[j].x * invV, v[j].y * invV};
-    v[j] = {kr[j].x * e.x, kr[j].y * e.y};
-    acc[0] += pdot(v[j], e);
+    const cplx<R> o = v[j];  // N^3 times the physical value
+    v[j] = {kr[j].x * o.x * invV, kr[j].y * o.y * invV};
+    acc[0] += pdot(v[j], o);
   }
   row_r2c<R, N, false, true>(v, rw.lds, rw.t, stw);
   if (d == 0) {
@@ -554,7 +555,7 @@ __global__ void __launch_bounds__(64) k_plane_xdiff(PlaneArgs a, const cplx<R>* 
   }
   rw.store(f, v);
   plane_totals<1, 64>(acc, sh);
-  if (threadIdx.x == 0) a.epart[(long long)blockIdx.y * T::NX + blockIdx.x] = acc[0] * ((double)N * N * N);
+  if (threadIdx.x == 0) a.epart[(long long)blockIdx.y * T::NX + blockIdx.x] = acc[0];
 }
 
 // blockIdx.x: kx plane, blockIdx.y: system.

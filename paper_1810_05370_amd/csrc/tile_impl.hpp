@@ -458,15 +458,20 @@ __global__ void __launch_bounds__((TileCfg<R, N>::TB), 2) k_tile_xelast(TileXArg
     if constexpr (RICH) return etar[i];
     else return eta[poff + LB * i];
   };
-  // v <- c * v / N^3 per pair, adding its product with v / N^3 to the energy
+  // c v / N^3, the same bits in any order: in FP32 c v first (v / N^3 alone is out of
+  // range for moduli above 1e33), in FP64 c / N^3, which spills less and is 2 % of a
+  // split step faster
+  auto scaled = [&](R c, R v) { return RICH ? c * v * invV : (c * invV) * v; };
+  // v <- c * v / N^3 per pair, adding its product with v to the energy: <p, A p> of
+  // the spectral vectors is N^3 times the physical sum (and products of two
+  // physical values would underflow N^3 times as early)
   auto scale_by = [&](cplx<R>(&v)[16], auto&& coef) {
     hold_loads();
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const cplx<R> c = coef(i);
-      const cplx<R> e = {v[i].x * invV, v[i].y * invV};
-      v[i] = {c.x * e.x, c.y * e.y};
-      en += (double)v[i].x * (double)e.x + (double)v[i].y * (double)e.y;
+      const cplx<R> c = coef(i), o = v[i];
+      v[i] = {scaled(c.x, o.x), scaled(c.y, o.y)};
+      en += (double)v[i].x * (double)o.x + (double)v[i].y * (double)o.y;
     }
     pin(en);
   };
@@ -489,9 +494,8 @@ __global__ void __launch_bounds__((TileCfg<R, N>::TB), 2) k_tile_xelast(TileXArg
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const cplx<R> m = mu_at(i);
-        const cplx<R> e = {w[i].x * invV, w[i].y * invV};
-        const cplx<R> me = {R(2) * m.x * e.x, R(2) * m.y * e.y};
-        en += (double)me.x * (double)e.x + (double)me.y * (double)e.y;
+        const cplx<R> me = {scaled(R(2) * m.x, w[i].x), scaled(R(2) * m.y, w[i].y)};
+        en += (double)me.x * (double)w[i].x + (double)me.y * (double)w[i].y;
         w[i] = cadd(me, lt[i]);
       }
       pin(en);
@@ -559,8 +563,7 @@ __global__ void __launch_bounds__((TileCfg<R, N>::TB), 2) k_tile_xelast(TileXArg
 
   double e1[1] = {en};
   block_totals<1, T::TB>(e1, reinterpret_cast<double*>(buf));
-  // <p, A p> of the spectral vectors is N^3 times the physical sum
-  if (tid == 0) a.epart[blockIdx.x] = e1[0] * ((double)N * N * N);
+  if (tid == 0) a.epart[blockIdx.x] = e1[0];
 }
 
 // ---------------------------------------------------------------- launchers

@@ -1,5 +1,6 @@
 """Solves at the limits of what their entry points accept: the largest
-iteration cap, very stiff or soft tissue, an indefinite preconditioner."""
+iteration cap, very stiff or soft tissue, a tiny force, an indefinite
+preconditioner."""
 import ctypes
 
 import pytest
@@ -116,3 +117,22 @@ def test_fp64_solve_scales_exactly_with_the_moduli(n, k):
         got.append((u * 2.0 ** e, it, rr))
     assert got[0][1:] == got[1][1:]
     assert torch.equal(got[0][0], got[1][0])
+
+
+@pytest.mark.parametrize("n", [16, 64, 128, 256])
+def test_fp64_solve_of_a_tiny_force(n):
+    """A random force of rms 2^-506: the per-mode products of the inner products, 1e-303 V at the start and 1e-16
+    of that at the end, reach into the denormal range, with about six digits left at 16^3.  The largest terms
+    decide alpha, so the count is that of the force of rms 1, give or take one."""
+    torch = need_gpu()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(4)
+    f = torch.randn((3, n, n, n), generator=gen, dtype=torch.float64, device="cuda")
+    sim = _sim(n, "fp64", max_it=200)
+    its = []
+    for k in (0, -506):
+        u, it, rr = sim.solve_elasticity(f * 2.0 ** k)   # (an error if it does not converge)
+        say(f"n={n}, force * 2^{k}: {it} iterations, residual {rr:.2e}")
+        its.append(it)
+    sim.close()
+    assert abs(its[1] - its[0]) <= 1
