@@ -344,9 +344,9 @@ __global__ void __launch_bounds__((TileCfg<R, N>::TA), (sizeof(R) == 4 ? 4 : 2))
 }
 
 // ------------------------------------------------------------------ x side
-// Ten row transforms in and nine out per row.  FP32 (0.39 ms at 256^3) keeps mu,
+// Ten row transforms in and nine out per row.  FP32 (0.38 ms at 256^3) keeps mu,
 // eta and the next inputs in registers and is bound by its instructions and LDS
-// accesses; FP64 (0.83 ms) has no room for them and moves 33 arrays at 5.4 TB/s,
+// accesses; FP64 (0.82 ms) has no room for them and moves 33 arrays at 5.4 TB/s,
 // the coefficient re-reads among them.
 template <typename R, int N>
 __global__ void __launch_bounds__((TileCfg<R, N>::TB), 2) k_tile_xelast(TileXArgs a, const cplx<R>* __restrict__ twg) {
